@@ -144,8 +144,6 @@ __device__ __forceinline__ uint32_t xcd_contiguous(uint32_t wg, uint32_t nwg) {
     return xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
 }
 
-
-
 // Where and how a call's launches go: the stream, and the most work-items of one dispatch (the
 // plan's limit).
 struct Exec {
@@ -161,5 +159,11 @@ int run_slot_passes(float* buf, int64_t elems, const trivance_plan_t* p, float* 
                     hipStream_t stream, int pb, int pe);
 int run_slot_passes(int* buf, int64_t elems, const trivance_plan_t* p, int* ws, hipStream_t stream,
                     int pb, int pe);
+
+// Whole bandwidth-optimal calls in one launch (fold.hip): whether plan and size allow it, and the
+// call.
+bool fold_fits(const trivance_plan_t* p, int64_t elems);
+int run_fold_call(float* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream);
+int run_fold_call(int* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream);
 
 }  // namespace trivance

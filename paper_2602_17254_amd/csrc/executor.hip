@@ -1065,10 +1065,11 @@ int64_t trivance_workspace_bytes(const trivance_plan_t* plan, int64_t elems, int
     return (int64_t)trivance::slot_halves(plan) * plan->max_slots * plan->n * elems * 4;
 }
 
-int trivance_allreduce_emulated_steps_ws(void* buffers, int n, int64_t elems, int dtype,
-                                         const trivance_plan_t* plan, void* workspace,
-                                         int64_t workspace_bytes, void* stream, int pass_begin,
-                                         int pass_end) {
+// Argument checks shared by every form; OK with *run = false for a valid call without work.
+static int check_call(void* buffers, int n, int64_t elems, int dtype, const trivance_plan_t* plan,
+                      void* workspace, int64_t workspace_bytes, int pass_begin, int pass_end,
+                      bool* run) {
+    *run = false;
     if (!plan || n != plan->n || elems < 0) return TRIVANCE_EINVAL;
     if (dtype != TRIVANCE_F32 && dtype != TRIVANCE_I32) return TRIVANCE_EINVAL;
     const int np = (int)plan->passes.size();
@@ -1078,6 +1079,18 @@ int trivance_allreduce_emulated_steps_ws(void* buffers, int n, int64_t elems, in
     if (!buffers) return TRIVANCE_EINVAL;
     const int64_t need = trivance_workspace_bytes(plan, elems, dtype);
     if (workspace_bytes < need || (need > 0 && !workspace)) return TRIVANCE_ESIZE;
+    *run = true;
+    return TRIVANCE_OK;
+}
+
+int trivance_allreduce_emulated_steps_ws(void* buffers, int n, int64_t elems, int dtype,
+                                         const trivance_plan_t* plan, void* workspace,
+                                         int64_t workspace_bytes, void* stream, int pass_begin,
+                                         int pass_end) {
+    bool run;
+    const int rc = check_call(buffers, n, elems, dtype, plan, workspace, workspace_bytes, pass_begin,
+                              pass_end, &run);
+    if (!run) return rc;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (dtype == TRIVANCE_F32)
         return trivance::run_passes<float>(static_cast<float*>(buffers), elems, plan,
@@ -1090,9 +1103,21 @@ int trivance_allreduce_emulated_ws(void* buffers, int n, int64_t elems, int dtyp
                                    const trivance_plan_t* plan, void* workspace,
                                    int64_t workspace_bytes, void* stream) {
     if (!plan) return TRIVANCE_EINVAL;
-    return trivance_allreduce_emulated_steps_ws(buffers, n, elems, dtype, plan, workspace,
-                                                workspace_bytes, stream, 0,
-                                                (int)plan->passes.size());
+    const int np = (int)plan->passes.size();
+    bool run;
+    const int rc = check_call(buffers, n, elems, dtype, plan, workspace, workspace_bytes, 0, np, &run);
+    if (!run) return rc;
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    if (trivance::fold_fits(plan, elems)) {
+        if (dtype == TRIVANCE_F32)
+            return trivance::run_fold_call(static_cast<float*>(buffers), elems, plan, s);
+        return trivance::run_fold_call(static_cast<int*>(buffers), elems, plan, s);
+    }
+    if (dtype == TRIVANCE_F32)
+        return trivance::run_passes<float>(static_cast<float*>(buffers), elems, plan,
+                                           static_cast<float*>(workspace), s, 0, np);
+    return trivance::run_passes<int>(static_cast<int*>(buffers), elems, plan,
+                                     static_cast<int*>(workspace), s, 0, np);
 }
 
 int trivance_allreduce_emulated_steps(void* buffers, int n, int64_t elems, int dtype,
@@ -1104,9 +1129,7 @@ int trivance_allreduce_emulated_steps(void* buffers, int n, int64_t elems, int d
 
 int trivance_allreduce_emulated(void* buffers, int n, int64_t elems, int dtype,
                                 const trivance_plan_t* plan, void* stream) {
-    if (!plan) return TRIVANCE_EINVAL;
-    return trivance_allreduce_emulated_steps(buffers, n, elems, dtype, plan, stream, 0,
-                                             (int)plan->passes.size());
+    return trivance_allreduce_emulated_ws(buffers, n, elems, dtype, plan, nullptr, 0, stream);
 }
 
 }  // extern "C"

@@ -62,6 +62,30 @@ struct DimTree {
     std::vector<std::vector<uint32_t>> alive;  // alive[m]: offsets not forwarded in steps < m
     std::vector<int> dirs;                     // step k: bit 0 a child sends towards +, bit 1 towards -
 };
+
+// Fold program of one collective of a bandwidth-optimal plan (fold_plan.h): 32-bit words with the
+// coordinates of an offset in the low kFoldCoordBits (kFoldCoordBits / D bits per dimension, the
+// collective's first dimension lowest) and what follows the row's load above them.
+constexpr int kMaxFoldDims = 4;
+constexpr int kFoldCoordBits = 24;
+constexpr uint32_t kFoldLeaf = 1u << 24;   // add to the open sum (otherwise: open a new one)
+constexpr uint32_t kFoldFirst = 1u << 25;  // starts the first sum
+constexpr uint32_t kFoldLast = 1u << 26;   // last node of its subtree
+constexpr int kFoldPopsShift = 27;         // sums closed after it, each added to the one below
+constexpr int kFoldMaxPops = 31;
+constexpr int kMaxFoldRanks = 8192;
+constexpr int kMaxFoldRoots = 512;
+constexpr size_t kMaxFoldWords = 896;      // words that fit the kernel arguments
+struct FoldProgram {
+    int cut = 0;
+    int sub_depth = 0, top_depth = 0;      // open sums below the current one, at most
+    std::vector<uint32_t> roots;           // subtrees in preorder: offset, and what follows
+    std::vector<uint32_t> shape;           // subtree -> its shape
+    std::vector<uint32_t> shape_begin;     // shape -> first node; nodes end with kFoldLast
+    std::vector<uint32_t> nodes;           // offsets from the subtree's root
+    // roots and their nodes' starts (16 bits each), then the nodes
+    size_t words() const { return roots.size() + (roots.size() + 1) / 2 + nodes.size(); }
+};
 }  // namespace trivance
 
 struct trivance_plan {
@@ -86,6 +110,10 @@ struct trivance_plan {
     // pass (same length as `passes`), and the most slots any state between passes holds.
     std::vector<trivance::SlotPass> slots;
     int max_slots = 0;
+    // Bandwidth-optimal plans: fold programs, and the one of every collective (empty: the plan runs
+    // step by step).
+    std::vector<trivance::FoldProgram> folds;
+    std::vector<int> fold_of;
 };
 
 namespace trivance {

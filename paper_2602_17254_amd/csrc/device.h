@@ -74,6 +74,23 @@ __device__ __forceinline__ void st(T* p, const Vec<T, N>& v) {
     }
 }
 
+// Rows whose length is no multiple of 16 bytes are read with 16-byte loads all the same: the
+// instructions need 4-byte alignment.
+template <typename T, int VEC, bool NT>
+__device__ __forceinline__ Vec<T, VEC> ld_any(const T* p) {
+    Vec<T, VEC> r;
+    if constexpr (VEC == 4) {
+        typedef T U __attribute__((ext_vector_type(4), aligned(4)));
+        const U* q = reinterpret_cast<const U*>(p);
+        const U x = NT ? __builtin_nontemporal_load(q) : *q;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r.v[i] = x[i];
+    } else {
+        r.v[0] = NT ? __builtin_nontemporal_load(p) : *p;
+    }
+    return r;
+}
+
 // Store of a write-once output through a raw buffer descriptor, with one of two instruction
 // cache policies chosen per pass by the host (`keep`, wave-uniform):
 //  * keep = 0: NT | SC1 (streaming). Passes over gigabytes measured 1-3.5% faster this way than
@@ -160,10 +177,5 @@ int run_slot_passes(float* buf, int64_t elems, const trivance_plan_t* p, float* 
 int run_slot_passes(int* buf, int64_t elems, const trivance_plan_t* p, int* ws, hipStream_t stream,
                     int pb, int pe);
 
-// Whole bandwidth-optimal calls in one launch (fold.hip): whether plan and size allow it, and the
-// call.
-bool fold_fits(const trivance_plan_t* p, int64_t elems);
-int run_fold_call(float* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream);
-int run_fold_call(int* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream);
 
 }  // namespace trivance

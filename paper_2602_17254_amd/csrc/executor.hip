@@ -2,7 +2,8 @@
 //
 // n virtual ranks keep their vectors as rows of one rank-major device array. One kernel launch
 // materialises one step of the schedule in place; the kernel boundary is the per-step barrier
-// of Sec. 4.3 (both incoming messages are reduced before the next step starts).
+// of Sec. 4.3 (both incoming messages are reduced before the next step starts). The step-range
+// calls run this way, and whole calls that no fused form takes (api.hip).
 //
 // Latency-optimal step (Sec. 4.2): every rank r of collective c computes
 //     x_r <- (x_r + x_{r - d e}) + x_{r + d e}     over its segment,
@@ -33,6 +34,7 @@
 #include <cstdint>
 #include <cstring>
 
+#include "calls.h"
 #include "device.h"
 #include "plan.h"
 
@@ -1054,82 +1056,15 @@ int run_passes(T* buf, int64_t elems, const trivance_plan_t* p, T* ws, hipStream
 }
 
 }  // namespace
+
+int run_step_passes(float* buf, int64_t elems, const trivance_plan_t* p, float* ws,
+                    hipStream_t stream, int pb, int pe) {
+    return run_passes(buf, elems, p, ws, stream, pb, pe);
+}
+
+int run_step_passes(int* buf, int64_t elems, const trivance_plan_t* p, int* ws, hipStream_t stream,
+                    int pb, int pe) {
+    return run_passes(buf, elems, p, ws, stream, pb, pe);
+}
+
 }  // namespace trivance
-
-extern "C" {
-
-int64_t trivance_workspace_bytes(const trivance_plan_t* plan, int64_t elems, int dtype) {
-    if (!plan || elems < 0) return TRIVANCE_EINVAL;
-    if (dtype != TRIVANCE_F32 && dtype != TRIVANCE_I32) return TRIVANCE_EINVAL;
-    if (plan->slots.empty()) return 0;
-    return (int64_t)trivance::slot_halves(plan) * plan->max_slots * plan->n * elems * 4;
-}
-
-// Argument checks shared by every form; OK with *run = false for a valid call without work.
-static int check_call(void* buffers, int n, int64_t elems, int dtype, const trivance_plan_t* plan,
-                      void* workspace, int64_t workspace_bytes, int pass_begin, int pass_end,
-                      bool* run) {
-    *run = false;
-    if (!plan || n != plan->n || elems < 0) return TRIVANCE_EINVAL;
-    if (dtype != TRIVANCE_F32 && dtype != TRIVANCE_I32) return TRIVANCE_EINVAL;
-    const int np = (int)plan->passes.size();
-    if (pass_begin < 0 || pass_end < pass_begin || pass_end > np) return TRIVANCE_EINVAL;
-    if (plan->variant == TRIVANCE_BRUCK_REF) return TRIVANCE_EUNSUPPORTED;
-    if (elems == 0 || pass_begin == pass_end) return TRIVANCE_OK;
-    if (!buffers) return TRIVANCE_EINVAL;
-    const int64_t need = trivance_workspace_bytes(plan, elems, dtype);
-    if (workspace_bytes < need || (need > 0 && !workspace)) return TRIVANCE_ESIZE;
-    *run = true;
-    return TRIVANCE_OK;
-}
-
-int trivance_allreduce_emulated_steps_ws(void* buffers, int n, int64_t elems, int dtype,
-                                         const trivance_plan_t* plan, void* workspace,
-                                         int64_t workspace_bytes, void* stream, int pass_begin,
-                                         int pass_end) {
-    bool run;
-    const int rc = check_call(buffers, n, elems, dtype, plan, workspace, workspace_bytes, pass_begin,
-                              pass_end, &run);
-    if (!run) return rc;
-    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (dtype == TRIVANCE_F32)
-        return trivance::run_passes<float>(static_cast<float*>(buffers), elems, plan,
-                                           static_cast<float*>(workspace), s, pass_begin, pass_end);
-    return trivance::run_passes<int>(static_cast<int*>(buffers), elems, plan,
-                                     static_cast<int*>(workspace), s, pass_begin, pass_end);
-}
-
-int trivance_allreduce_emulated_ws(void* buffers, int n, int64_t elems, int dtype,
-                                   const trivance_plan_t* plan, void* workspace,
-                                   int64_t workspace_bytes, void* stream) {
-    if (!plan) return TRIVANCE_EINVAL;
-    const int np = (int)plan->passes.size();
-    bool run;
-    const int rc = check_call(buffers, n, elems, dtype, plan, workspace, workspace_bytes, 0, np, &run);
-    if (!run) return rc;
-    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (trivance::fold_fits(plan, elems)) {
-        if (dtype == TRIVANCE_F32)
-            return trivance::run_fold_call(static_cast<float*>(buffers), elems, plan, s);
-        return trivance::run_fold_call(static_cast<int*>(buffers), elems, plan, s);
-    }
-    if (dtype == TRIVANCE_F32)
-        return trivance::run_passes<float>(static_cast<float*>(buffers), elems, plan,
-                                           static_cast<float*>(workspace), s, 0, np);
-    return trivance::run_passes<int>(static_cast<int*>(buffers), elems, plan,
-                                     static_cast<int*>(workspace), s, 0, np);
-}
-
-int trivance_allreduce_emulated_steps(void* buffers, int n, int64_t elems, int dtype,
-                                      const trivance_plan_t* plan, void* stream, int pass_begin,
-                                      int pass_end) {
-    return trivance_allreduce_emulated_steps_ws(buffers, n, elems, dtype, plan, nullptr, 0, stream,
-                                                pass_begin, pass_end);
-}
-
-int trivance_allreduce_emulated(void* buffers, int n, int64_t elems, int dtype,
-                                const trivance_plan_t* plan, void* stream) {
-    return trivance_allreduce_emulated_ws(buffers, n, elems, dtype, plan, nullptr, 0, stream);
-}
-
-}  // extern "C"

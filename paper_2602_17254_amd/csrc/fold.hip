@@ -1,22 +1,35 @@
-// Whole bandwidth-optimal AllReduce in one launch, for gfx950: the fold kernel and its launcher. The
-// fold programs come from fold_plan.h.
+// Whole bandwidth-optimal AllReduce for gfx950: each vector is read once and written once. The fold
+// kernel adds up every column over the rows in the order of the block's reduction tree (the
+// programs come from fold_plan.h), so the results are the step kernels', bit for bit; the
+// result goes to every row, as the all-gather's copies would carry it.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstdint>
 #include <cstring>
-#ifdef FOLD_TUNE
-#include <cstdlib>
-#endif
 
+#include "calls.h"
 #include "device.h"
 #include "plan.h"
 
 namespace trivance {
 namespace {
 
-constexpr int kFoldBatch = 8;  // rows whose loads a wave issues together
-constexpr int kStreamWaves = 4;
+// What the split and the layout rest on (MI355X, 16x16x16 ranks of 4 MiB unless said otherwise).
+// One read and one write of every vector at the rate of a plain copy (6.76 TB/s) take 5.08 ms; the
+// 18 step launches took 22.3 ms, fold and spread take 4.91.
+//  * Two launches. Waves that read their column of all rows and then write it to all rows drift
+//    apart, and with reads and writes of many rows mixed the memory gave 5.0-5.5 TB/s whatever
+//    the store policy, occupancy or batch. Reads alone reach 6.9-7.1, and one-store waves that
+//    walk the rows in address order 7.0-7.4. So the fold only writes row 0, and spread_kernel
+//    copies it. The one-launch form stays for calls below kSpreadBytes.
+//  * The scalar unit bounds the reads next: a wave's kibibyte may take 91 cycles of its compute
+//    unit, and decoding one row per program word took about as many. One word for the up to
+//    three rows of V(o, 1) cut the read part from 3.58 to 2.5 ms.
+//  * Three nodes (up to nine loads) in flight per wave: two or four measured the same, six 18%
+//    slower (128 instead of 96 registers).
+constexpr int kFoldBatch = 3;
+constexpr int kStreamWaves = 4;  // tiles of a workgroup when a wave has a tile of its own
 
 struct FoldArgs {
     int64_t elems;
@@ -30,32 +43,17 @@ struct FoldArgs {
     uint32_t tail_tile;                  // the tile of the last elems % 4 columns (or beyond all)
     uint32_t nroots[kMaxFoldDims];       // per collective: its program in tab
     uint32_t root0[kMaxFoldDims], start0[kMaxFoldDims], node0[kMaxFoldDims];
+    uint32_t dim0[kMaxFoldDims];         // dimension of the collective's first step
     uint32_t steps;                      // placed plans: reduce-scatter steps
     uint32_t pdim[kMaxFoldDims];         // and the dimension of step t in bits 4 t .. 4 t + 3
     int placed;
     int sub_depth, top_depth;
     uint32_t lanes;                      // column vectors of a tile
     uint32_t wg_base;
-    int keep;
+    int spread;                          // 1: the result goes to row 0 only (spread_kernel follows)
     uint32_t tab[kMaxFoldWords];
 };
 static_assert(sizeof(FoldArgs) <= 4096, "fold kernel arguments above 4 KiB");
-
-// Rows whose length is no multiple of 16 bytes are read with 16-byte loads all the same: the
-// instructions need 4-byte alignment.
-template <typename T, int VEC>
-__device__ __forceinline__ Vec<T, VEC> ld_row(const T* p) {
-    Vec<T, VEC> r;
-    if constexpr (VEC == 4) {
-        typedef T U __attribute__((ext_vector_type(4), aligned(4)));
-        const U x = __builtin_nontemporal_load(reinterpret_cast<const U*>(p));
-#pragma unroll
-        for (int i = 0; i < 4; ++i) r.v[i] = x[i];
-    } else {
-        r.v[0] = __builtin_nontemporal_load(p);
-    }
-    return r;
-}
 
 // One tile: `lanes` column vectors of every row. P waves evaluate the subtrees of the cut (P = 1:
 // a wave of its own, which also combines them as it goes).
@@ -80,7 +78,7 @@ __device__ __forceinline__ void fold_tile(T* __restrict__ buf, const FoldArgs& a
     const uint32_t cl = lane < nvec ? lane : nvec - 1;
     const T* const col = buf + col0 + (int64_t)cl * VEC;
 
-    // the block of this lane's columns and its coordinates, in the order of dimensions c, c + 1, ...
+    // the block of this lane's columns and its coordinates
     const uint32_t gr = (uint32_t)((col0 - seg_b + (int64_t)cl * VEC) / kGranule);
     uint32_t j;
     if (a.narrow) {
@@ -88,10 +86,9 @@ __device__ __forceinline__ void fold_tile(T* __restrict__ buf, const FoldArgs& a
     } else {
         j = (uint32_t)(((uint64_t)(gr + 1) * a.n - 1) / (uint64_t)(a.seg_g[c + 1] - a.seg_g[c]));
     }
-    uint32_t x[D], side[D], stride[D];
+    uint32_t y[D] = {};
     if (a.placed) {
         // j is the block's position: its base-3 digits, the last step's lowest
-        uint32_t y[D] = {};
         for (int t = (int)a.steps - 1; t >= 0; --t) {
             const uint32_t j3 = __umulhi(j, 0xAAAAAAABu) >> 1;
             const uint32_t dim = (a.pdim[c] >> (4 * t)) & 15u;
@@ -101,43 +98,32 @@ __device__ __forceinline__ void fold_tile(T* __restrict__ buf, const FoldArgs& a
                 if (dim == (uint32_t)d) y[d] = 3u * y[d] + digit;
             j = j3;
         }
-#pragma unroll
-        for (int f = 0; f < D; ++f) {
-            const int d = c + f < D ? c + f : c + f - D;
-#pragma unroll
-            for (int q = 0; q < D; ++q)
-                if (q == d) x[f] = y[q];
-        }
     } else {
-        uint32_t y[D];
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             const uint32_t q = d + 1 < D ? fdiv32(j, a.f_side[d]) : 0u;
             y[d] = j - q * a.side[d];
-            if (d + 1 == D) y[d] = j;
             j = q;
         }
-#pragma unroll
-        for (int f = 0; f < D; ++f) {
-            const int d = c + f < D ? c + f : c + f - D;
-#pragma unroll
-            for (int q = 0; q < D; ++q)
-                if (q == d) x[f] = y[q];
-        }
     }
+    // in the order of dimensions dim0, dim0 + 1, ... (cyclic), as in the program
+    uint32_t x[D], side[D], stride[D];
 #pragma unroll
     for (int f = 0; f < D; ++f) {
-        const int d = c + f < D ? c + f : c + f - D;
+        const uint32_t d = a.dim0[c] + f < (uint32_t)D ? a.dim0[c] + f : a.dim0[c] + f - D;
         side[f] = a.side[d];
         stride[f] = a.stride[d];
+        x[f] = y[0];
+#pragma unroll
+        for (int q = 1; q < D; ++q)
+            if ((uint32_t)q == d) x[f] = y[q];
     }
     constexpr int kBits = kFoldCoordBits / D;
     constexpr uint32_t kMask = (1u << kBits) - 1u;
     const uint64_t row_bytes = (uint64_t)E * sizeof(T);
 
     // the wave's part of the local memory: sums open below the current one
-    V* const sub = lds + (P == 1 ? wave * (uint32_t)(a.sub_depth + a.top_depth) * 64u
-                                 : (a.nroots[c] + 1u + wave * (uint32_t)a.sub_depth) * W);
+    V* const sub = lds + (P == 1 ? 0u : (a.nroots[c] + 1u + wave * (uint32_t)a.sub_depth) * W);
     const uint32_t SW = P == 1 ? 64u : W;          // vectors of one open sum
     const uint32_t sl = P == 1 ? lane : (lane < W ? lane : W - 1);
     V* const top = P == 1 ? sub + a.sub_depth * 64 : lds + (a.nroots[c] + 1u + P * (uint32_t)a.sub_depth) * W;
@@ -155,7 +141,7 @@ __device__ __forceinline__ void fold_tile(T* __restrict__ buf, const FoldArgs& a
             ++tp;
             tcur = val;
         }
-        for (uint32_t k = rw >> kFoldPopsShift; k > 0; --k) {
+        for (uint32_t k = (rw >> kFoldPopsShift) & kFoldMaxPops; k > 0; --k) {
             --tp;
             tcur = vadd(top[tp * SW + sl], tcur);
         }
@@ -166,36 +152,42 @@ __device__ __forceinline__ void fold_tile(T* __restrict__ buf, const FoldArgs& a
     const uint32_t* const starts = a.tab + a.start0[c];
     const uint32_t* const nodes = a.tab + a.node0[c];
     uint32_t g = P == 1 ? 0u : wave;
-    uint32_t rw = 0, pos = 0, r0[D];
+    uint32_t rw = 0, pos = 0, xr[D];  // the open subtree: its word, its next node, its root's coordinates
+    auto wrap = [](uint32_t v, uint32_t n) {  // v mod n for v < 2 n
+        const uint32_t z = v - n;
+        return v < z ? v : z;  // z wraps around when v < n
+    };
     auto open_root = [&]() {
         rw = roots[g];
         pos = (starts[g >> 1] >> (16 * (g & 1u))) & 0xFFFFu;
 #pragma unroll
-        for (int f = 0; f < D; ++f) r0[f] = (rw >> (f * kBits)) & kMask;
+        for (int f = 0; f < D; ++f) xr[f] = wrap(x[f] + ((rw >> (f * kBits)) & kMask), side[f]);
     };
     if (g < nroots) open_root();
     while (g < nroots) {
-        V v[kFoldBatch];
+        V vo[kFoldBatch], vl[kFoldBatch], vr[kFoldBatch];
         uint32_t w[kFoldBatch], rws[kFoldBatch], gs[kFoldBatch];
+        int live = 0;
 #pragma unroll
         for (int u = 0; u < kFoldBatch; ++u) {
-            w[u] = kFoldLast | kFoldFirst | kFoldLeaf;
-            rws[u] = gs[u] = ~0u;
             if (g < nroots) {
+                live = u + 1;
                 w[u] = nodes[pos];
                 rws[u] = rw;
                 gs[u] = g;
-                uint32_t row = 0;
+                uint32_t z[D], rest = 0;
 #pragma unroll
                 for (int f = 0; f < D; ++f) {
-                    uint32_t s = r0[f] + ((w[u] >> (f * kBits)) & kMask);
-                    s = s >= side[f] ? s - side[f] : s;
-                    const uint32_t y = x[f] + s;
-                    const uint32_t z = y - side[f];
-                    row += (y < z ? y : z) * stride[f];  // z wraps around when y < side
+                    z[f] = wrap(xr[f] + ((w[u] >> (f * kBits)) & kMask), side[f]);
+                    if (f) rest += z[f] * stride[f];
                 }
-                v[u] = ld_row<T, VEC>(reinterpret_cast<const T*>(
-                    reinterpret_cast<const char*>(col) + row * row_bytes));
+                auto at = [&](uint32_t z0) {
+                    return ld_any<T, VEC, true>(reinterpret_cast<const T*>(
+                        reinterpret_cast<const char*>(col) + (rest + z0 * stride[0]) * row_bytes));
+                };
+                vo[u] = at(z[0]);
+                if (w[u] & kFoldLeft) vl[u] = at(wrap(z[0] + side[0] - 1u, side[0]));
+                if (w[u] & kFoldRight) vr[u] = at(wrap(z[0] + 1u, side[0]));
                 if (w[u] & kFoldLast) {
                     g += P;
                     if (g < nroots) open_root();
@@ -206,19 +198,22 @@ __device__ __forceinline__ void fold_tile(T* __restrict__ buf, const FoldArgs& a
         }
 #pragma unroll
         for (int u = 0; u < kFoldBatch; ++u) {
-            if (gs[u] == ~0u) continue;
+            if (u >= live) break;
+            V val = vo[u];
+            if (w[u] & kFoldLeft) val = vadd(val, vl[u]);
+            if (w[u] & kFoldRight) val = vadd(val, vr[u]);
             if (w[u] & kFoldFirst) {
-                cur = v[u];
+                cur = val;
             } else if (w[u] & kFoldLeaf) {
-                cur = vadd(cur, v[u]);
-                for (uint32_t k = w[u] >> kFoldPopsShift; k > 0; --k) {
+                cur = vadd(cur, val);
+                for (uint32_t k = (w[u] >> kFoldPopsShift) & kFoldMaxPops; k > 0; --k) {
                     --sp;
                     cur = vadd(sub[sp * SW + sl], cur);
                 }
             } else {
                 sub[sp * SW + sl] = cur;
                 ++sp;
-                cur = v[u];
+                cur = val;
             }
             if (w[u] & kFoldLast) {
                 if constexpr (P == 1) add_root(rws[u], cur);
@@ -231,8 +226,9 @@ __device__ __forceinline__ void fold_tile(T* __restrict__ buf, const FoldArgs& a
         const uint32_t nbytes = nvec * VEC * (uint32_t)sizeof(T);
         const uint32_t off = lane * VEC * (uint32_t)sizeof(T);
         T* out = buf + col0;
-        for (uint32_t r = 0; r < a.n; ++r, out += E)
-            st_out<T, VEC>(buffer_rsrc(out, nbytes), off, tcur, a.keep);
+        const uint32_t rows = a.spread ? 1u : a.n;
+        for (uint32_t r = 0; r < rows; ++r, out += E)
+            st_out_as<1>(buffer_rsrc(out, nbytes), off, tcur);
     } else {
         __syncthreads();
         V* const res = lds + nroots * W;
@@ -245,10 +241,10 @@ __device__ __forceinline__ void fold_tile(T* __restrict__ buf, const FoldArgs& a
         const uint32_t per = 64u / W, lr = lane / W, lc = lane - lr * W;
         const V val = res[lc];
         const uint32_t off = (uint32_t)(lr * row_bytes) + lc * VEC * (uint32_t)sizeof(T);
-        for (uint32_t r = wave * per; r < a.n; r += P * per)
-            if (lc < nvec && r + lr < a.n)
-                st_out<T, VEC>(buffer_rsrc(buf + col0 + (int64_t)r * E, 0xFFFFFFFFu), off, val,
-                               a.keep);
+        const uint32_t rows = a.spread ? 1u : a.n;
+        for (uint32_t r = wave * per; r < rows; r += P * per)
+            if (lc < nvec && r + lr < rows)
+                st_out_as<1>(buffer_rsrc(buf + col0 + (int64_t)r * E, 0xFFFFFFFFu), off, val);
     }
 }
 
@@ -257,31 +253,140 @@ __global__ __launch_bounds__(64 * (P == 1 ? kStreamWaves : P)) void fold_kernel(
                                                                                 FoldArgs a) {
     extern __shared__ __align__(16) char lds[];
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t wg = a.wg_base + blockIdx.x;
+    const uint32_t wg = a.wg_base + xcd_contiguous(blockIdx.x, gridDim.x);
     const uint32_t tile = P == 1 ? wg * kStreamWaves + wave : wg;
     if (tile >= a.tile_end[D - 1]) return;
+    // waves with a tile of their own: a part of the local memory each, of the size of whole vectors
+    // also where the tile is the tail
+    char* const mine = P == 1 ? lds + wave * (uint32_t)(a.sub_depth + a.top_depth) * 64u * 16u : lds;
     if (tile == a.tail_tile)
-        fold_tile<T, 1, D, P>(buf, a, tile, wave, reinterpret_cast<Vec<T, 1>*>(lds));
+        fold_tile<T, 1, D, P>(buf, a, tile, wave, reinterpret_cast<Vec<T, 1>*>(mine));
     else
-        fold_tile<T, 4, D, P>(buf, a, tile, wave, reinterpret_cast<Vec<T, 4>*>(lds));
+        fold_tile<T, 4, D, P>(buf, a, tile, wave, reinterpret_cast<Vec<T, 4>*>(mine));
+}
+
+// Copies row 0 to every other row. One wave stores up to 64 vectors of one row; consecutive waves
+// walk the tiles of one panel of a row, then the next row, then the next panel.
+//  * One store per wave, in address order: 7.0-7.4 TB/s where the all-gather steps' two stores per
+//    load gave 6.2; three or more rows per wave gave 5.5-6.4.
+//  * A panel of 4096 tiles (4 MiB of row 0) stays in the L2 caches while all rows are written, and
+//    a multiple of 8 workgroups per panel row keeps each XCD on its own eighth of it. Panels of
+//    0.5, 1 and 2 MiB measured 25, 16 and 7% slower on the 9x9x9 torus at 8 MiB, 8 MiB the same,
+//    64 MiB 10% slower on the ring of 8.
+//  * A row whose length is no multiple of 128 bytes starts inside a cache line. Its tiles are
+//    shifted so that every store but the row's first and last ones covers whole lines.
+struct SpreadArgs {
+    int64_t elems;
+    uint32_t n1;          // rows to write: n - 1
+    uint32_t tiles;       // per row
+    uint32_t panel;       // tiles of a panel
+    uint32_t units;       // n1 * tiles
+    FastDiv32 f_full;     // panel * n1
+    FastDiv32 f_panel, f_last;  // panel, tiles of the last one
+    uint32_t wg_base;
+    int shifted;
+};
+constexpr uint32_t kSpreadTile = 256;  // elements of one wave
+constexpr uint32_t kSpreadPanel = 4096;
+constexpr int kSpreadWaves = 4;
+
+template <typename T>
+__global__ __launch_bounds__(64 * kSpreadWaves) void spread_kernel(T* __restrict__ buf,
+                                                                   SpreadArgs a) {
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t unit = (a.wg_base + blockIdx.x) * kSpreadWaves + wave;
+    if (unit >= a.units) return;
+    const uint32_t p = fdiv32(unit, a.f_full);
+    const uint32_t rest = unit - p * a.panel * a.n1;
+    const bool last = (p + 1) * a.panel > a.tiles;
+    const uint32_t width = last ? a.tiles - p * a.panel : a.panel;
+    const uint32_t r = fdiv32(rest, last ? a.f_last : a.f_panel);
+    const int64_t E = a.elems;
+    T* const dst = buf + (int64_t)(r + 1) * E;
+    int64_t col = (int64_t)(p * a.panel + (rest - r * width)) * kSpreadTile + lane * 4;
+    // elements of the row before its first whole cache line: tile 0 ends there
+    if (a.shifted)
+        col -= kSpreadTile - ((0u - (uint32_t)(reinterpret_cast<uintptr_t>(dst) / sizeof(T))) & 31u);
+    const BufI4 rs = buffer_rsrc(dst, (uint32_t)(E * (int64_t)sizeof(T)));
+    if (col >= 0 && col + 4 <= E) {
+        st_out_as<0>(rs, (uint32_t)col * (uint32_t)sizeof(T), ld_any<T, 4, false>(buf + col));
+    } else {
+        for (int i = 0; i < 4; ++i)
+            if (col + i >= 0 && col + i < E)
+                st_out_as<0>(rs, (uint32_t)(col + i) * (uint32_t)sizeof(T), Vec<T, 1>{{buf[col + i]}});
+    }
+}
+
+template <typename T>
+hipError_t launch_spread(T* buf, int64_t elems, const trivance_plan_t* p, const Exec& x) {
+    SpreadArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.elems = elems;
+    a.n1 = (uint32_t)p->n - 1;
+    a.shifted = elems % 32 != 0 || (uintptr_t)buf % 128 != 0 ? 1 : 0;
+    a.tiles = (uint32_t)((elems + kSpreadTile - 1) / kSpreadTile) + (a.shifted ? 1u : 0u);
+    a.panel = std::min(kSpreadPanel, a.tiles);
+    a.units = a.n1 * a.tiles;
+    a.f_full = make_fastdiv32(a.panel * a.n1);
+    a.f_panel = make_fastdiv32(a.panel);
+    a.f_last = make_fastdiv32(a.tiles % a.panel ? a.tiles % a.panel : a.panel);
+    hipError_t err = hipSuccess;
+    for_each_dispatch(((uint64_t)a.units + kSpreadWaves - 1) / kSpreadWaves, 64 * kSpreadWaves,
+                      x.items, [&](uint32_t first, uint32_t count) {
+        a.wg_base = first;
+        hipLaunchKernelGGL((spread_kernel<T>), dim3(count), dim3(64 * kSpreadWaves), 0, x.stream,
+                           buf, a);
+        err = hipGetLastError();
+        return err == hipSuccess;
+    });
+    return err;
 }
 
 struct FoldShape {
+    int spread;      // 1: result to row 0, spread_kernel copies it
     int waves;       // waves per tile
     uint32_t lanes;  // column vectors of a tile
 };
 
+size_t fold_lds(const FoldShape& s, size_t roots, int sub_depth, int top_depth) {
+    if (s.waves == 1) return (size_t)kStreamWaves * (sub_depth + top_depth) * 64 * 16;
+    return (roots + 1 + (size_t)s.waves * sub_depth + top_depth) * s.lanes * 16;
+}
+
+// Fold and spread from 192 MiB of vectors on. Measured in us, one launch against two, at 134 MB
+// (ring of 8) 45.7 / 46.3, at 191 MB (27x27) 68.4 / 65.9, at 255 MB (ring of 243) 88 / 81, at 268 MB
+// (rings of 4 and 64) 91 / 81 and 92 / 82: below the size of the 256 MB last-level cache the writes
+// of the one launch end there, and the second launch costs 3 us.
+constexpr int64_t kSpreadBytes = (int64_t)192 << 20;
+// A wave per tile from 2048 tiles of 1 KiB on (524,288 elements): it needs no local memory for the
+// subtrees and no barrier. With fewer tiles that leaves compute units idle, so sixteen waves share
+// one. In us, sixteen waves against one: 32x32 ranks at 524,288 elements 717 / 631, at 262,144
+// 364 / 427, at 65,536 97 / 298; 16x16x16 at 524,288 3576 / 2743, at 262,144 1852 / 1957; 27x27 at
+// 16,384 23 / 168.
+constexpr int64_t kStreamVecs = (int64_t)2048 * 64;
+// With at most eight subtrees four waves share a tile (more would find none). Tiles narrow down
+// to 64 bytes while there are fewer than one per compute unit: 27x27 ranks of 4096 elements 26
+// us with 1 KiB tiles, 20 with 256 B and 19 with 64 B.
+constexpr int64_t kComputeUnits = 256;
+// Local memory of a tile's subtrees: all of a compute unit's if need be. 32x32 ranks of 65,536
+// elements took 117 us with tiles narrowed to fit 64 KiB and 97 with 156 KiB.
+constexpr size_t kFoldLds = 156 * 1024;
+
 inline FoldShape fold_shape(const trivance_plan_t* p, int64_t elems) {
-    FoldShape s{1, 64};
-    const int64_t tiles = (elems + 255) / 256;
-    if (tiles < 2048) s = FoldShape{16, 64};
-    if (tiles < 256) s = FoldShape{16, 16};
-#ifdef FOLD_TUNE
-    if (const char* e = std::getenv("FOLD_P")) s.waves = std::atoi(e);
-    if (const char* e = std::getenv("FOLD_W")) s.lanes = (uint32_t)std::atoi(e);
-#endif
-    if (s.waves > 1)
-        while (s.lanes > 4 && p->folds[0].roots.size() * s.lanes * 16 > 56 * 1024) s.lanes /= 4;
+    size_t roots = 0;
+    int sub_depth = 0, top_depth = 0;
+    for (const FoldProgram& f : p->folds) {
+        roots = std::max(roots, f.roots.size());
+        sub_depth = std::max(sub_depth, f.sub_depth);
+        top_depth = std::max(top_depth, f.top_depth);
+    }
+    const int64_t vecs = (elems + 3) / 4;
+    FoldShape s{(int64_t)p->n * elems * 4 >= kSpreadBytes ? 1 : 0, 1, 64};
+    if (vecs >= kStreamVecs) return s;
+    s.waves = roots > 8 ? 16 : 4;
+    while (s.lanes > 4 && vecs < kComputeUnits * (int64_t)s.lanes) s.lanes /= 2;
+    while (s.lanes > 4 && fold_lds(s, roots, sub_depth, top_depth) > kFoldLds) s.lanes /= 2;
     return s;
 }
 
@@ -308,9 +413,9 @@ int run_fold_dims(T* buf, int64_t elems, const trivance_plan_t* p, hipStream_t s
     a.elems = elems;
     a.n = (uint32_t)p->n;
     a.lanes = s.lanes;
+    a.spread = s.spread;
     a.placed = p->placed ? 1 : 0;
     a.steps = (uint32_t)p->S;
-    a.keep = 2 * (int64_t)p->n * elems * 4 <= kKeepPassBytes ? 1 : 0;
     const int64_t G = (elems + kGranule - 1) / kGranule;
     int64_t max_gc = 0;
     for (int c = 0; c <= D; ++c) a.seg_g[c] = (int64_t)c * G / D;
@@ -352,6 +457,7 @@ int run_fold_dims(T* buf, int64_t elems, const trivance_plan_t* p, hipStream_t s
         for (int c = 0; c < D; ++c) {
             if (c >= c0 && c < c1) {
                 const FoldProgram& fp = p->folds[p->fold_of[c]];
+                a.dim0[c] = (uint32_t)p->fold_dim0[c];
                 a.nroots[c] = (uint32_t)fp.roots.size();
                 a.root0[c] = at[p->fold_of[c]];
                 a.start0[c] = a.root0[c] + a.nroots[c];
@@ -363,18 +469,17 @@ int run_fold_dims(T* buf, int64_t elems, const trivance_plan_t* p, hipStream_t s
             a.tile_end[c] = tiles;
         }
         if (tiles == 0) continue;
-        size_t lds;
+        const size_t lds = fold_lds(s, most_roots, a.sub_depth, a.top_depth);
         hipError_t err;
-        if (s.waves == 1) {
-            lds = (size_t)kStreamWaves * (a.sub_depth + a.top_depth) * 64 * 16;
+        if (s.waves == 1)
             err = launch_fold<T, D, 1>(buf, a, (tiles + kStreamWaves - 1) / kStreamWaves, lds, x);
-        } else {
-            lds = (most_roots + 1 + (size_t)s.waves * a.sub_depth + a.top_depth) * s.lanes * 16;
-            if (s.waves == 4) err = launch_fold<T, D, 4>(buf, a, tiles, lds, x);
-            else err = launch_fold<T, D, 16>(buf, a, tiles, lds, x);
-        }
+        else if (s.waves == 4)
+            err = launch_fold<T, D, 4>(buf, a, tiles, lds, x);
+        else
+            err = launch_fold<T, D, 16>(buf, a, tiles, lds, x);
         if (err != hipSuccess) return TRIVANCE_EHIP;
     }
+    if (s.spread && launch_spread(buf, elems, p, x) != hipSuccess) return TRIVANCE_EHIP;
     return TRIVANCE_OK;
 }
 
@@ -391,7 +496,8 @@ int run_fold(T* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream
 }  // namespace
 
 bool fold_fits(const trivance_plan_t* p, int64_t elems) {
-    return !p->folds.empty() && elems < ((int64_t)1 << 28);
+    return !p->folds.empty() && elems < ((int64_t)1 << 28) &&
+           (int64_t)p->n * ((elems + kSpreadTile - 1) / kSpreadTile + 1) < ((int64_t)1 << 31) - 4;
 }
 
 int run_fold_call(float* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream) {

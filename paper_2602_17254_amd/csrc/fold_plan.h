@@ -10,6 +10,9 @@
 // of open sums performs the schedule's own adds, in its own association, while it reads every row
 // once. The all-gather only copies the result to every rank.
 //
+// The first step always joins a row with its neighbours at distance 1, so a program node stands for
+// V(o, 1): up to three rows under one word.
+//
 // The walk is cut at one step: V(o, cut) is evaluated by the subprogram of its shape, and the
 // sums of the subtrees (the "roots" of the cut, in preorder) are combined by the steps from `cut` on.
 // Subtrees of one shape differ by a translation only and share one subprogram, so the program of
@@ -37,8 +40,12 @@ struct FoldWalk {
     struct Node {
         int o[kMaxFoldDims];
         bool leaf, first;
-        int pops;
+        uint32_t pops;
     };
+
+    uint32_t children(const int* o, int t) const {
+        return (*flags)[rs[t].dim[c]][rs[t].taken[c][rs[t].dim[c]]][o[rs[t].dim[c]]];
+    }
 
     // V(o, T) over the steps [tmin, T), appended to out.
     void visit(const int* o, int tmin, int T, bool first, std::vector<Node>* out) const {
@@ -50,9 +57,8 @@ struct FoldWalk {
         out->push_back(node);
         for (int t = tmin; t < T; ++t) {
             const int a = rs[t].dim[c];
-            const int k = rs[t].taken[c][a];
             const int side = p->dims[a], dist = rs[t].distance[c];
-            const uint32_t f = (*flags)[a][k][o[a]];
+            const uint32_t f = children(o, t);
             for (int q = 0; q < 2; ++q) {
                 if (!(f & (q == 0 ? kFromLeft : kFromRight))) continue;
                 int child[kMaxFoldDims];
@@ -71,8 +77,8 @@ struct FoldWalk {
 
 inline uint32_t fold_word(const FoldWalk::Node& nd, int D, int c, const int* rel,
                           const int* dims) {
-    // coordinates in the order of dimensions c, c + 1, ... (cyclic): collectives of a torus with
-    // equal sides then share one program
+    // coordinates in the order of dimensions c, c + 1, ... (cyclic; c: that of the first step):
+    // collectives of a torus with equal sides then share one program
     const int bits = kFoldCoordBits / D;
     uint32_t w = 0;
     for (int f = 0; f < D; ++f) {
@@ -82,7 +88,7 @@ inline uint32_t fold_word(const FoldWalk::Node& nd, int D, int c, const int* rel
     }
     if (nd.leaf) w |= kFoldLeaf;
     if (nd.first) w |= kFoldFirst;
-    return w | ((uint32_t)nd.pops << kFoldPopsShift);
+    return w | (nd.pops << kFoldPopsShift);
 }
 
 // Largest number of sums open besides the current one.
@@ -90,7 +96,7 @@ inline int fold_depth(const std::vector<FoldWalk::Node>& nodes) {
     int sp = 0, most = 0;
     for (const FoldWalk::Node& nd : nodes) {
         if (!nd.first && !nd.leaf) most = std::max(most, ++sp);
-        sp -= nd.pops;
+        sp -= (int)nd.pops;
     }
     return most;
 }
@@ -105,21 +111,24 @@ inline bool fold_program(const FoldWalk& w, int S, int cut, bool uniform, FoldPr
     *out = FoldProgram();
     if ((int)top.size() > kMaxFoldRoots) return false;
     out->cut = cut;
+    const int dim0 = w.rs[0].dim[w.c];
     out->top_depth = fold_depth(top);
     std::map<std::vector<uint32_t>, int> seen;
     for (const FoldWalk::Node& r : top) {
         if (r.pops > kFoldMaxPops) return false;
-        out->roots.push_back(fold_word(r, p->D, w.c, zero, p->dims));
+        out->roots.push_back(fold_word(r, p->D, dim0, zero, p->dims));
         if (uniform && !out->shape.empty()) {
             out->shape.push_back(0u);
             continue;
         }
         sub.clear();
-        w.visit(r.o, 0, cut, true, &sub);
+        w.visit(r.o, 1, cut, true, &sub);
         std::vector<uint32_t> words;
         for (const FoldWalk::Node& nd : sub) {
             if (nd.pops > kFoldMaxPops) return false;
-            words.push_back(fold_word(nd, p->D, w.c, r.o, p->dims));
+            const uint32_t f = w.children(nd.o, 0);
+            words.push_back(fold_word(nd, p->D, dim0, r.o, p->dims) |
+                            (f & kFromLeft ? kFoldLeft : 0u) | (f & kFromRight ? kFoldRight : 0u));
         }
         words.back() |= kFoldLast;
         const auto ins = seen.emplace(words, (int)out->shape_begin.size());
@@ -152,6 +161,7 @@ inline void build_fold_programs(trivance_plan_t* p, const std::vector<DimTree>& 
     // steps taken before, per dimension (the power-of-three passes do not carry them)
     std::vector<Pass> rs(p->passes.begin(), p->passes.begin() + p->S);
     for (int c = 0; c < p->D; ++c) {
+        if (rs[0].distance[c] != 1) return;
         int count[kMaxDims] = {};
         for (int t = 0; t < p->S; ++t) {
             for (int d = 0; d < p->D; ++d) rs[t].taken[c][d] = count[d];
@@ -165,8 +175,8 @@ inline void build_fold_programs(trivance_plan_t* p, const std::vector<DimTree>& 
         while (v % 3 == 0) v /= 3;
         uniform = uniform && v == 1;
     }
-    // The cut: the same step for every collective, of the first half the one with the fewest words
-    // in all. Any cut gives the same adds; near the middle there are few roots and few nodes per
+    // The cut: the same step for every collective, from 1 to half of them the one with the fewest
+    // words in all. Any cut gives the same adds; near the middle there are few roots and few nodes per
     // shape. On equal sides every collective has the first one's program (its dimensions renamed).
     const int ncoll = equal ? 1 : p->D;
     std::vector<FoldProgram> best;
@@ -186,7 +196,10 @@ inline void build_fold_programs(trivance_plan_t* p, const std::vector<DimTree>& 
     }
     if (best.empty()) return;
     p->folds.swap(best);
-    for (int c = 0; c < p->D; ++c) p->fold_of.push_back(equal ? 0 : c);
+    for (int c = 0; c < p->D; ++c) {
+        p->fold_of.push_back(equal ? 0 : c);
+        p->fold_dim0.push_back(rs[0].dim[c]);
+    }
 }
 
 }  // namespace trivance

@@ -63,16 +63,19 @@ struct DimTree {
     std::vector<int> dirs;                     // step k: bit 0 a child sends towards +, bit 1 towards -
 };
 
-// Fold program of one collective of a bandwidth-optimal plan (fold_plan.h): 32-bit words with the
+// Fold program of one collective of a bandwidth-optimal plan (fold_plan.h). Words hold the
 // coordinates of an offset in the low kFoldCoordBits (kFoldCoordBits / D bits per dimension, the
-// collective's first dimension lowest) and what follows the row's load above them.
+// dimension of the collective's first step lowest, then the next ones cyclically) and what
+// to do with the value above them.
 constexpr int kMaxFoldDims = 4;
 constexpr int kFoldCoordBits = 24;
 constexpr uint32_t kFoldLeaf = 1u << 24;   // add to the open sum (otherwise: open a new one)
 constexpr uint32_t kFoldFirst = 1u << 25;  // starts the first sum
-constexpr uint32_t kFoldLast = 1u << 26;   // last node of its subtree
-constexpr int kFoldPopsShift = 27;         // sums closed after it, each added to the one below
-constexpr int kFoldMaxPops = 31;
+constexpr int kFoldPopsShift = 26;         // sums closed after it, each added to the one below
+constexpr uint32_t kFoldMaxPops = 7;
+constexpr uint32_t kFoldLast = 1u << 29;   // last node of its subtree
+constexpr uint32_t kFoldLeft = 1u << 30;   // the row's neighbours of the first step that are added
+constexpr uint32_t kFoldRight = 1u << 31;  // to the row at once
 constexpr int kMaxFoldRanks = 8192;
 constexpr int kMaxFoldRoots = 512;
 constexpr size_t kMaxFoldWords = 896;      // words that fit the kernel arguments
@@ -110,10 +113,10 @@ struct trivance_plan {
     // pass (same length as `passes`), and the most slots any state between passes holds.
     std::vector<trivance::SlotPass> slots;
     int max_slots = 0;
-    // Bandwidth-optimal plans: fold programs, and the one of every collective (empty: the plan runs
-    // step by step).
+    // Bandwidth-optimal plans: fold programs, the one of every collective and the dimension of its
+    // first step (empty: the plan runs step by step).
     std::vector<trivance::FoldProgram> folds;
-    std::vector<int> fold_of;
+    std::vector<int> fold_of, fold_dim0;
 };
 
 namespace trivance {

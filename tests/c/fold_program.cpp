@@ -62,7 +62,7 @@ struct Fold {
         if (w & trivance::kFoldFirst) cur = v;
         else if (w & trivance::kFoldLeaf) cur += v;
         else open.push_back(cur), cur = v;
-        for (uint32_t k = w >> trivance::kFoldPopsShift; k > 0; --k) cur = open.back() + cur, open.pop_back();
+        for (uint32_t k = (w >> trivance::kFoldPopsShift) & trivance::kFoldMaxPops; k > 0; --k) cur = open.back() + cur, open.pop_back();
     }
 };
 
@@ -97,15 +97,21 @@ static int check(const char* text) {
                 for (uint32_t pos = f.shape_begin[f.shape[g]];; ++pos) {
                     if (pos >= f.nodes.size()) return 2;
                     const uint32_t w = f.nodes[pos];
-                    int row = 0;
+                    int row = 0, left = 0, right = 0;  // the node's row and its neighbours' at distance 1
                     for (int i = 0; i < D; ++i) {
-                        const int d = (c + i) % D;
+                        const int d = (p->fold_dim0[c] + i) % D;
                         const uint32_t mask = (1u << bits) - 1u;
-                        row += (int)((((f.roots[g] >> (i * bits)) & mask) + ((w >> (i * bits)) & mask) +
-                                      (uint32_t)coord(p, j, d)) % (uint32_t)dims[d]) * p->strides[d];
+                        const int y = (int)((((f.roots[g] >> (i * bits)) & mask) + ((w >> (i * bits)) & mask) +
+                                             (uint32_t)coord(p, j, d)) % (uint32_t)dims[d]);
+                        row += y * p->strides[d];
+                        left += (i ? y : (y + dims[d] - 1) % dims[d]) * p->strides[d];
+                        right += (i ? y : (y + 1) % dims[d]) * p->strides[d];
                     }
                     ++seen[row];
-                    sub.node(w & ~trivance::kFoldLast, x[row]);
+                    float v = x[row];
+                    if (w & trivance::kFoldLeft) ++seen[left], v += x[left];
+                    if (w & trivance::kFoldRight) ++seen[right], v += x[right];
+                    sub.node(w, v);
                     if ((int)sub.open.size() > f.sub_depth) return 3;
                     if (w & trivance::kFoldLast) break;
                 }

@@ -1,0 +1,88 @@
+"""Whole bandwidth-optimal calls (fold.hip) against the schedule's steps.
+
+CPU: every fold program visits each row once and performs the steps' own adds
+(tests/c/fold_program.cpp, plan.cpp built with g++). GPU: the whole call gives the same bits as the
+same plan run one pass at a time through trivance_allreduce_emulated_steps, on every shape the
+launcher distinguishes; the other GPU tests compare the whole call with the oracle."""
+
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2602_17254_amd", "csrc")
+SIDES = """2 3 4 5 6 7 8 9 10 13 16 25 26 27 28 50 64 81 100 128 200 243 256 299 300 729 2x2 3x3 3x27
+9x27 27x27 5x7 4x8 9x8 8x64 32x32 16x16 4x4x4 9x9x9 9x9x3 8x8x8 2x2x2 16x16x16 2x3x4 3x5x7x4 1x9
+9x1x8""".split()
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not found")
+def test_fold_programs_perform_the_schedules_adds(tmp_path):
+    exe = str(tmp_path / "fold_program")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", CSRC,
+                    "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                    os.path.join(ROOT, "tests", "c", "fold_program.cpp"),
+                    os.path.join(CSRC, "plan.cpp"), "-o", exe], check=True)
+    res = subprocess.run([exe, *SIDES], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stdout + res.stderr
+    assert "0 failures" in res.stdout
+
+
+# (dims, elems, dtype, placement, elements the buffer starts beyond an aligned address, dispatch
+# limit). Tiles of four and of sixteen waves at their narrowest and widest, a wave per tile, one launch
+# and two (192 MiB and more), a tail of 1 to 3 columns, segments of less than a tile, rows
+# that start inside a cache line, and launches split over several dispatches.
+CASES = [
+    ((2,), 257, "f32", "natural", 0, None),
+    ((8,), 1, "f32", "natural", 0, None),
+    ((7,), 524288 + 3, "i32", "natural", 1, None),
+    ((5, 7), 255, "f32", "natural", 3, None),
+    ((1, 9), 3001, "f32", "natural", 0, None),
+    ((27, 27), 4098, "f32", "natural", 0, 1024),
+    ((243,), 16 * 1024 + 5, "f32", "natural", 2, None),
+    ((32, 32), 16384 + 2, "i32", "natural", 0, None),
+    ((16, 16, 16), 259, "f32", "natural", 0, None),
+    ((9, 9, 9), 4100, "f32", "schedule", 0, 1024),
+    ((8, 64), 5001, "f32", "natural", 0, None),
+    ((3, 5, 7, 4), 6001, "f32", "natural", 0, None),
+    ((3,), 17_000_001, "f32", "natural", 0, None),
+    ((4, 4, 4), 786_436, "i32", "natural", 0, 1 << 20),
+    ((3, 27), 640_007, "f32", "schedule", 1, None),
+    ((243,), 262_145, "f32", "natural", 0, None),
+    ((32, 32), 65_537, "f32", "natural", 3, None),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"{'x'.join(map(str, c[0]))}-E{c[1]}-{c[2]}"
+                                                      f"-{c[3]}-o{c[4]}-l{c[5]}")
+def test_whole_call_equals_the_steps(case):
+    import torch
+
+    import paper_2602_17254_amd as T
+
+    dims, E, dtype, placement, offset, limit = case
+    n = int(np.prod(dims))
+    print(f"[fold] {case}", flush=True)
+    plan = T.trivance_plan(dims, "B", placement)
+    if limit:
+        plan = T.trivance_plan_with_dispatch_limit(plan, limit)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + E)
+    if dtype == "f32":
+        V = torch.randn(n * E, generator=g, device="cuda")
+    else:
+        V = torch.randint(-2 ** 31, 2 ** 31 - 1, (n * E,), generator=g, device="cuda",
+                          dtype=torch.int32)
+    got = torch.empty(n * E + offset + 64, dtype=V.dtype, device="cuda").fill_(7)
+    whole = got[offset:offset + n * E].copy_(V).view(n, E)
+    steps = V.view(n, E)
+    T.trivance_allreduce_emulated(whole, plan)
+    for p in range(plan.num_passes):
+        T.trivance_allreduce_emulated_steps(steps, plan, p, p + 1)
+    torch.cuda.synchronize()
+    assert torch.equal(whole.view(torch.int32), steps.view(torch.int32))
+    assert bool((got[:offset] == 7).all()) and bool((got[offset + n * E:] == 7).all())

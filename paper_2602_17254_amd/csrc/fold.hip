@@ -368,7 +368,6 @@ constexpr int64_t kStreamVecs = (int64_t)2048 * 64;
 // With at most eight subtrees four waves share a tile (more would find none). Tiles narrow down
 // to 64 bytes while there are fewer than one per compute unit: 27x27 ranks of 4096 elements 26
 // us with 1 KiB tiles, 20 with 256 B and 19 with 64 B.
-constexpr int64_t kComputeUnits = 256;
 // Local memory of a tile's subtrees: all of a compute unit's if need be. 32x32 ranks of 65,536
 // elements took 117 us with tiles narrowed to fit 64 KiB and 97 with 156 KiB.
 constexpr size_t kFoldLds = 156 * 1024;
@@ -385,7 +384,7 @@ inline FoldShape fold_shape(const trivance_plan_t* p, int64_t elems) {
     FoldShape s{(int64_t)p->n * elems * 4 >= kSpreadBytes ? 1 : 0, 1, 64};
     if (vecs >= kStreamVecs) return s;
     s.waves = roots > 8 ? 16 : 4;
-    while (s.lanes > 4 && vecs < kComputeUnits * (int64_t)s.lanes) s.lanes /= 2;
+    while (s.lanes > 4 && vecs < (int64_t)kComputeUnits * s.lanes) s.lanes /= 2;
     while (s.lanes > 4 && fold_lds(s, roots, sub_depth, top_depth) > kFoldLds) s.lanes /= 2;
     return s;
 }

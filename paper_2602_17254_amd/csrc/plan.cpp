@@ -16,6 +16,7 @@
 
 #include "fold_plan.h"
 #include "plan.h"
+#include "sweep_plan.h"
 
 using trivance::kGranule;
 using trivance::kMaxDims;
@@ -551,6 +552,7 @@ int trivance_plan_ex(int n, const int* torus_dims, int ndims, int variant, unsig
             rc = variant == TRIVANCE_BANDWIDTH_OPT ? build_tree_plan(p) : build_latency_slot_plan(p);
             if (rc == TRIVANCE_OK && variant == TRIVANCE_BANDWIDTH_OPT)
                 trivance::build_fold_programs(p, p->trees);
+            if (rc == TRIVANCE_OK && variant == TRIVANCE_LATENCY_OPT) trivance::build_sweep_programs(p);
         } catch (const std::bad_alloc&) {
             rc = TRIVANCE_ENOMEM;
         }
@@ -597,6 +599,7 @@ int trivance_plan_ex(int n, const int* torus_dims, int ndims, int variant, unsig
         } else {
             for (int t = 0; t < p->S; ++t)
                 p->passes.push_back(make_pass(p, *rot, TRIVANCE_PHASE_LATENCY, t));
+            if (variant == TRIVANCE_LATENCY_OPT) trivance::build_sweep_programs(p);
         }
     } catch (const std::bad_alloc&) {
         delete rot;

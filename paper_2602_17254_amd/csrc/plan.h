@@ -89,6 +89,22 @@ struct FoldProgram {
     // roots and their nodes' starts (16 bits each), then the nodes
     size_t words() const { return roots.size() + (roots.size() + 1) / 2 + nodes.size(); }
 };
+
+// Column program of one collective of a latency-optimal plan (sweep_plan.h). An operation is four
+// words: its terms (coordinates of the displacement in the low bits, kSweepCoordBits / D per
+// dimension, dimension c first, and the slot of the array above them; kSweepNone: no third term),
+// then the slot of its result.
+constexpr int kMaxSweepDims = 4;
+constexpr int kSweepCoordBits = 24;
+constexpr uint32_t kSweepNone = 0xFFFFFFFFu;
+constexpr int kMaxSweepRanks = 4096;
+constexpr size_t kMaxSweepWords = 896;
+struct SweepProgram {
+    std::vector<uint32_t> words;
+    std::vector<uint32_t> level_begin;  // first operation of every level, and the end
+    int max_ops = 0;                    // most operations of one level
+    int slots = 0;                      // arrays in on-chip memory at a time
+};
 }  // namespace trivance
 
 struct trivance_plan {
@@ -117,6 +133,9 @@ struct trivance_plan {
     // first step (empty: the plan runs step by step).
     std::vector<trivance::FoldProgram> folds;
     std::vector<int> fold_of, fold_dim0;
+    // Latency-optimal plans: column programs, one for all collectives on equal sides, otherwise one
+    // per collective (empty: the plan runs step by step).
+    std::vector<trivance::SweepProgram> sweeps;
 };
 
 namespace trivance {

@@ -1,0 +1,80 @@
+"""Whole latency-optimal calls (sweep.hip) against the schedule's steps.
+
+CPU: every column program performs the steps' own adds (tests/c/sweep_program.cpp, plan.cpp built
+with g++). GPU: the whole call gives the same bits as the same plan run one pass at a time through
+trivance_allreduce_emulated_steps_ws, on every shape the launcher distinguishes; the other GPU
+tests compare the whole call with the oracle."""
+
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2602_17254_amd", "csrc")
+SIDES = """2 3 4 5 7 8 9 10 16 27 32 64 81 100 128 200 243 256 299 300 729 2x2 3x3 9x9 9x9x9 27x27 3x27
+9x27 32x32 16x16 8x8 4x4 8x64 4x8 9x8 5x7 4x4x4 8x8x8 2x3x4 1x9 9x1x8 3x3x3x3""".split()
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not found")
+def test_column_programs_perform_the_schedules_adds(tmp_path):
+    exe = str(tmp_path / "sweep_program")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", CSRC,
+                    "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                    os.path.join(ROOT, "tests", "c", "sweep_program.cpp"),
+                    os.path.join(CSRC, "plan.cpp"), "-o", exe], check=True)
+    res = subprocess.run([exe, *SIDES], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stdout + res.stderr
+    assert "0 failures" in res.stdout
+
+
+# (dims, elems, dtype, elements the buffer starts beyond an aligned address, dispatch limit): one, up
+# to four and up to twelve operations a level; one, two and four cells to a thread; one tile and
+# several to a workgroup; the widest and narrowest tiles, columns that end inside a vector and a
+# segment of less than a tile; one to four dimensions; launches split over several dispatches.
+CASES = [
+    ((2,), 1001, "f32", 0, None), ((3,), 4099, "f32", 1, None), ((5,), 3, "f32", 0, None),
+    ((8,), 70_001, "i32", 3, None), ((9,), 70_003, "f32", 0, 1024), ((27,), 33_000, "f32", 0, None),
+    ((64,), 20_002, "f32", 2, 1024), ((81,), 40_001, "i32", 0, None), ((243,), 9_001, "f32", 0, None),
+    ((300,), 5_003, "f32", 1, None), ((729,), 4_099, "f32", 0, None), ((1, 9), 1001, "f32", 0, None),
+    ((9, 9), 26_215, "i32", 1, None), ((5, 7), 3_001, "f32", 0, None),
+    ((16, 16), 9_001, "f32", 0, 65536), ((32, 32), 4_101, "f32", 3, None),
+    ((8, 64), 4_102, "f32", 0, None), ((8, 8, 8), 5_001, "i32", 0, None),
+    ((9, 9, 9), 7_003, "f32", 1, None), ((2, 3, 4), 129, "f32", 0, None),
+    ((3, 3, 3, 3), 2_001, "f32", 0, None),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"{'x'.join(map(str, c[0]))}-E{c[1]}-{c[2]}"
+                                                      f"-o{c[3]}-l{c[4]}")
+def test_whole_call_equals_the_steps(case):
+    import torch
+
+    import paper_2602_17254_amd as T
+
+    dims, E, dtype, offset, limit = case
+    n = int(np.prod(dims))
+    print(f"[sweep] {case}", flush=True)
+    plan = T.trivance_plan(dims, "L")
+    if limit:
+        plan = T.trivance_plan_with_dispatch_limit(plan, limit)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + E)
+    if dtype == "f32":
+        V = torch.randn(n * E, generator=g, device="cuda")
+    else:
+        V = torch.randint(-2 ** 31, 2 ** 31 - 1, (n * E,), generator=g, device="cuda",
+                          dtype=torch.int32)
+    ws = torch.empty(max(16, T.trivance_workspace_bytes(plan, E)), dtype=torch.uint8, device="cuda")
+    got = torch.empty(n * E + offset + 64, dtype=V.dtype, device="cuda").fill_(7)
+    whole = got[offset:offset + n * E].copy_(V).view(n, E)
+    steps = V.view(n, E)
+    T.trivance_allreduce_emulated_ws(whole, plan, ws)
+    for p in range(plan.num_passes):
+        T.trivance_allreduce_emulated_steps_ws(steps, plan, ws, p, p + 1)
+    torch.cuda.synchronize()
+    assert torch.equal(whole.view(torch.int32), steps.view(torch.int32))
+    assert bool((got[:offset] == 7).all()) and bool((got[offset + n * E:] == 7).all())

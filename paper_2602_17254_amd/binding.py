@@ -206,34 +206,46 @@ def trivance_pass_bytes(plan: Plan, elems: int, pass_index: int, dtype: int = F3
                   "trivance_pass_bytes")
 
 
-def _stream_ptr(stream):
-    import torch
+_TORCH = None
+_DTYPES = {}
 
+
+def _torch():
+    """The torch module, and the element types it maps to; imported on the first call."""
+    global _TORCH
+    if _TORCH is None:
+        import torch
+
+        _DTYPES.update({torch.float32: F32, torch.int32: I32})
+        _TORCH = torch
+    return _TORCH
+
+
+def _stream_ptr(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        # the current stream's handle as current_stream().cuda_stream gives it, without the Stream
+        # object: 0.3 us instead of 2.7 (a whole small AllReduce takes 8 with it and 5 without)
+        c = _torch()._C
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _buffer_args(buffers, plan: Plan):
-    import torch
-
-    if not isinstance(buffers, torch.Tensor) or not buffers.is_cuda:
+    if not isinstance(buffers, _torch().Tensor) or not buffers.is_cuda:
         raise TypeError("buffers must be a CUDA (HIP) torch tensor")
-    if buffers.dim() != 2 or buffers.shape[0] != plan.n or not buffers.is_contiguous():
+    shape = buffers.shape
+    if len(shape) != 2 or shape[0] != plan.n or not buffers.is_contiguous():
         raise ValueError(f"buffers must be a contiguous [{plan.n}, elems] tensor")
-    if buffers.dtype == torch.float32:
-        dt = F32
-    elif buffers.dtype == torch.int32:
-        dt = I32
-    else:
+    dt = _DTYPES.get(buffers.dtype)
+    if dt is None:
         raise TypeError("buffers must be float32 or int32")
-    return ctypes.c_void_p(buffers.data_ptr()), plan.n, buffers.shape[1], dt
+    return buffers.data_ptr(), plan.n, shape[1], dt
 
 
 def trivance_allreduce_emulated(buffers, plan: Plan, stream=None) -> None:
     """In-place emulated AllReduce over the rows of `buffers` (enqueued on `stream`)."""
     ptr, n, E, dt = _buffer_args(buffers, plan)
-    _check(_lib().trivance_allreduce_emulated(ptr, n, E, dt, plan.handle, _stream_ptr(stream)),
+    _check(_lib().trivance_allreduce_emulated(ptr, n, E, dt, plan._h, _stream_ptr(stream)),
            "trivance_allreduce_emulated")
 
 
@@ -251,14 +263,12 @@ def trivance_workspace_bytes(plan: Plan, elems: int, dtype: int = F32) -> int:
 
 
 def _workspace_args(workspace):
-    import torch
-
     if workspace is None:
-        return ctypes.c_void_p(0), 0
-    if not isinstance(workspace, torch.Tensor) or not workspace.is_cuda or \
+        return None, 0
+    if not isinstance(workspace, _torch().Tensor) or not workspace.is_cuda or \
             not workspace.is_contiguous():
         raise TypeError("workspace must be a contiguous CUDA tensor")
-    return ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size()
+    return workspace.data_ptr(), workspace.numel() * workspace.element_size()
 
 
 def trivance_allreduce_emulated_ws(buffers, plan: Plan, workspace, stream=None) -> None:

@@ -30,6 +30,7 @@ int check_call(void* buffers, int n, int64_t elems, int dtype, const trivance_pl
 // run step by step.
 template <typename T>
 int run_whole(T* buf, int64_t elems, const trivance_plan_t* plan, T* ws, hipStream_t stream) {
+    if (trivance::tile_fits(plan, elems)) return trivance::run_tile_call(buf, elems, plan, stream);
     if (trivance::fold_fits(plan, elems)) return trivance::run_fold_call(buf, elems, plan, stream);
     if (trivance::sweep_fits(plan, elems))
         return trivance::run_sweep_call(buf, elems, plan, stream);

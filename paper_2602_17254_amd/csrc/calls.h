@@ -22,6 +22,11 @@ bool fold_fits(const trivance_plan_t* p, int64_t elems);
 int run_fold_call(float* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream);
 int run_fold_call(int* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream);
 
+// Small ones of these in tiles of local memory (tile.hip).
+bool tile_fits(const trivance_plan_t* p, int64_t elems);
+int run_tile_call(float* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream);
+int run_tile_call(int* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream);
+
 // The same for whole latency-optimal calls (sweep.hip).
 bool sweep_fits(const trivance_plan_t* p, int64_t elems);
 int run_sweep_call(float* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream);

@@ -143,6 +143,41 @@ inline bool fold_program(const FoldWalk& w, int S, int cut, bool uniform, FoldPr
     return out->words() <= kMaxFoldWords;
 }
 
+// The trees by offset (kMaxTileSteps in plan.h); none if they do not fit.
+inline void build_tile_masks(trivance_plan_t* p, const std::vector<DimTree>& trees,
+                             const std::vector<Pass>& rs) {
+    p->tile_masks.clear();
+    p->tile_mask0.clear();
+    if (p->S > kMaxTileSteps) return;
+    std::vector<uint32_t> words, first;
+    std::map<std::vector<uint32_t>, uint32_t> seen;
+    for (int c = 0; c < p->D; ++c)
+        for (int d = 0; d < p->D; ++d) {
+            std::vector<uint32_t> w(p->dims[d], 31u << kTileForwardShift);
+            for (int t = 0; t < p->S; ++t) {
+                if (rs[t].dim[c] != d) continue;
+                const int k = rs[t].taken[c][d];
+                for (uint32_t r : trees[d].recv[k]) {
+                    const uint32_t o = r & ~(kFromLeft | kFromRight);
+                    if (r & kFromLeft) w[o] |= 1u << (2 * t);
+                    if (r & kFromRight) w[o] |= 2u << (2 * t);
+                }
+                // forwarded in step k: there before it and not after
+                std::vector<bool> after(p->dims[d], false);
+                for (uint32_t o : trees[d].alive[k + 1]) after[o] = true;
+                for (uint32_t o : trees[d].alive[k])
+                    if (!after[o])
+                        w[o] = (w[o] & ((1u << kTileForwardShift) - 1u)) | (uint32_t)t << kTileForwardShift;
+            }
+            const auto ins = seen.emplace(w, (uint32_t)words.size());
+            if (ins.second) words.insert(words.end(), w.begin(), w.end());
+            first.push_back(ins.first->second);
+        }
+    if (words.size() > kMaxTileWords) return;
+    p->tile_masks.swap(words);
+    p->tile_mask0.swap(first);
+}
+
 // Builds the fold programs of a bandwidth-optimal plan of S reduce-scatter steps. A plan they do not
 // fit (more ranks or dimensions, sides that do not fit a word's fields, too many words) keeps
 // none and runs step by step.
@@ -168,6 +203,7 @@ inline void build_fold_programs(trivance_plan_t* p, const std::vector<DimTree>& 
             count[rs[t].dim[c]] += 1;
         }
     }
+    build_tile_masks(p, trees, rs);
     bool equal = true, uniform = true;
     for (int d = 0; d < p->D; ++d) {
         equal = equal && p->dims[d] == p->dims[0];

@@ -90,6 +90,15 @@ struct FoldProgram {
     size_t words() const { return roots.size() + (roots.size() + 1) / 2 + nodes.size(); }
 };
 
+// Reduction trees by offset, for tiles in local memory (tile.hip): per (collective, dimension) one word
+// for every offset from a block's owner along that dimension, with bits 2 t and 2 t + 1 set if a
+// rank at that offset receives from the left and from the right in step t, and from kTileForwardShift
+// on the step in which it forwards (31: the owner's own coordinate). A rank takes part in
+// step t while no dimension's offset has been forwarded.
+constexpr int kMaxTileSteps = 13;
+constexpr int kTileForwardShift = 26;
+constexpr size_t kMaxTileWords = 832;
+
 // Column program of one collective of a latency-optimal plan (sweep_plan.h). An operation is four
 // words: its terms (coordinates of the displacement in the low bits, kSweepCoordBits / D per
 // dimension, dimension c first, and the slot of the array above them; kSweepNone: no third term),
@@ -133,6 +142,9 @@ struct trivance_plan {
     // first step (empty: the plan runs step by step).
     std::vector<trivance::FoldProgram> folds;
     std::vector<int> fold_of, fold_dim0;
+    // and their trees by offset, with the first word of (collective, dimension) at entry
+    // collective * D + dimension (empty: no tiles in local memory).
+    std::vector<uint32_t> tile_masks, tile_mask0;
     // Latency-optimal plans: column programs, one for all collectives on equal sides, otherwise one
     // per collective (empty: the plan runs step by step).
     std::vector<trivance::SweepProgram> sweeps;

@@ -1,8 +1,10 @@
 // Fold programs (fold_plan.h) against the schedule they replace, on the host: for every block of
 // every collective the program, read as the fold kernel reads it, must visit each row exactly once
 // and give the bits of the block's reduce-scatter steps run one after another on floats whose
-// sums depend on the association. Built with g++ against plan.cpp; no GPU. Exit status 0 on success.
+// sums depend on the association; the trees by offset (tile.hip) likewise. Built with g++ against plan.cpp; no GPU. Exit status 0 on success.
 //   fold_program SIDES...    (a ring "9", a torus "5x7")
+#include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -51,6 +53,35 @@ static float by_steps(const trivance_plan_t* p, int c, int j, std::vector<float>
         }
         x.swap(y);
         ++taken[a];
+    }
+    return x[j];
+}
+
+// The same from the trees by offset (tile_masks), as the tile kernel runs them.
+static float by_masks(const trivance_plan_t* p, int c, int j, std::vector<float> x) {
+    std::vector<uint32_t> mask(p->n);
+    for (int r = 0; r < p->n; ++r) {
+        uint32_t bits = 0, until = 31;
+        for (int d = 0; d < p->D; ++d) {
+            const int o = (coord(p, r, d) - coord(p, j, d) + p->dims[d]) % p->dims[d];
+            const uint32_t w = p->tile_masks.at(p->tile_mask0.at(c * p->D + d) + o);
+            bits |= w;
+            until = std::min(until, w >> trivance::kTileForwardShift);
+        }
+        until = std::min<uint32_t>(until, trivance::kMaxTileSteps);
+        mask[r] = bits & ((1u << (2 * until)) - 1u);
+    }
+    for (int t = 0; t < p->S; ++t) {
+        const int a = p->passes[t].dim[c], dist = p->passes[t].distance[c];
+        for (int r = 0; r < p->n; ++r) {
+            // in place: a rank that is read in a step does not receive in it
+            const uint32_t f = (mask[r] >> (2 * t)) & 3u;
+            const int xa = coord(p, r, a), side = p->dims[a];
+            const int l = r + ((xa - dist + side) % side - xa) * p->strides[a];
+            const int q = r + ((xa + dist) % side - xa) * p->strides[a];
+            if (f & 1u) x[r] += ((mask[l] >> (2 * t)) & 3u) ? NAN : x[l];
+            if (f & 2u) x[r] += ((mask[q] >> (2 * t)) & 3u) ? NAN : x[q];
+        }
     }
     return x[j];
 }
@@ -123,6 +154,8 @@ static int check(const char* text) {
             for (int s : seen) bad |= s != 1;
             const float want = by_steps(p, c, j, x);
             bad |= std::memcmp(&want, &top.cur, sizeof(float)) != 0;
+            const float tiled = p->tile_masks.empty() ? want : by_masks(p, c, j, x);
+            bad |= std::memcmp(&want, &tiled, sizeof(float)) != 0;
         }
     }
     trivance_plan_destroy(p);

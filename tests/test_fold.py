@@ -1,6 +1,6 @@
-"""Whole bandwidth-optimal calls (fold.hip) against the schedule's steps.
+"""Whole bandwidth-optimal calls (tile.hip, fold.hip) against the schedule's steps.
 
-CPU: every fold program visits each row once and performs the steps' own adds
+CPU: every fold program visits each row once and performs the steps' own adds, and so do the tiles
 (tests/c/fold_program.cpp, plan.cpp built with g++). GPU: the whole call gives the same bits as the
 same plan run one pass at a time through trivance_allreduce_emulated_steps, on every shape the
 launcher distinguishes; the other GPU tests compare the whole call with the oracle."""
@@ -32,7 +32,7 @@ def test_fold_programs_perform_the_schedules_adds(tmp_path):
 
 
 # (dims, elems, dtype, placement, elements the buffer starts beyond an aligned address, dispatch
-# limit). Tiles of four and of sixteen waves at their narrowest and widest, a wave per tile, one launch
+# limit). Small calls in local memory (one, two, four and eight cells to a thread), tiles of four and of sixteen waves at their narrowest and widest, a wave per tile, one launch
 # and two (192 MiB and more), a tail of 1 to 3 columns, segments of less than a tile, rows
 # that start inside a cache line, and launches split over several dispatches.
 CASES = [
@@ -45,6 +45,13 @@ CASES = [
     ((243,), 16 * 1024 + 5, "f32", "natural", 2, None),
     ((32, 32), 16384 + 2, "i32", "natural", 0, None),
     ((16, 16, 16), 259, "f32", "natural", 0, None),
+    ((16, 16, 16), 4096, "i32", "natural", 0, None),
+    ((16, 16, 16), 4099, "f32", "natural", 2, None),
+    ((9, 9, 9), 10_001, "f32", "schedule", 0, None),
+    ((27,), 100_003, "i32", "natural", 1, None),
+    ((20, 20, 20), 70, "f32", "natural", 0, None),
+    ((300,), 20_481, "f32", "natural", 0, 1024),
+    ((243,), 40_005, "f32", "natural", 0, 1 << 16),
     ((9, 9, 9), 4100, "f32", "schedule", 0, 1024),
     ((8, 64), 5001, "f32", "natural", 0, None),
     ((3, 5, 7, 4), 6001, "f32", "natural", 0, None),

@@ -12,7 +12,9 @@ every timed AllReduce works on the workload's own finite inputs. HIP events on t
 bracket each step and, inside it, each phase (all passes of the latency-optimal variant; the
 reduce-scatter and the all-gather), whose passes run back to back with one kernel family: group
 time / launches is that family's average launch duration, used for the roofline. One more step after the timed region brackets every pass
-with events (per-pass diagnostic only). Throughput counts the algorithmic
+with events (per-pass diagnostic only). The timed steps run pass by pass (the step-range calls),
+every step materialised in HBM; `whole_call` reports the same AllReduce through the whole-call
+form, which reads and writes each vector once and leaves the same bits. Throughput counts the algorithmic
 bytes of the step-by-step schedule (each participating location read once and each output
 written once per pass; trivance_algorithmic_bytes).
 
@@ -47,31 +49,31 @@ HBM_PEAK_GBPS = 8000.0  # MI355X HBM3E, AMD published peak
 # summaries are profiles/<kernel>_<workload>.md.
 MEASURED_TRAFFIC = {
     ("ring243_B_32MiB", "block_step_kernel<reduce>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 3248038769},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 3248115371},
     ("ring243_B_32MiB", "block_step_kernel<copy>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 2436096862},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 2436120196},
     ("ring243_Bp_32MiB", "block_step_kernel<reduce>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 3248046986},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 3248121592},
     ("ring243_Bp_32MiB", "block_step_kernel<copy>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 2436110148},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 2436134609},
     ("torus27x27_B_4MiB", "block_step_kernel<reduce>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 1017880301},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 1017904470},
     ("torus27x27_B_4MiB", "block_step_kernel<copy>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 763434309},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 763442011},
     ("torus27x27_Bp_4MiB", "block_step_kernel<reduce>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 1017886445},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 1017910571},
     ("torus27x27_Bp_4MiB", "block_step_kernel<copy>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 763454489},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 763462405},
     ("torus9x9x9_B_128MiB", "block_step_kernel<reduce>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 32569005959},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 32569730996},
     ("torus9x9x9_B_128MiB", "block_step_kernel<copy>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 24427297009},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 24427538689},
     ("torus9x9x9_Bp_128MiB", "block_step_kernel<reduce>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 32568970997},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 32569736798},
     ("torus9x9x9_Bp_128MiB", "block_step_kernel<copy>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 24427303559},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 24427558828},
     ("ring81_L_8MiB", "latency_split_kernel"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 1358961457},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 1358980999},
     ("ring64_L_8MiB", "slot_step_kernel"): {
         "src": "slot.hip", "src_sha": "2693a8a624b314e0", "bytes_per_launch": 3233243988},
     ("ring8_L_8MiB", "slot_step_kernel"): {
@@ -79,25 +81,25 @@ MEASURED_TRAFFIC = {
     ("torus32x32_L_8MiB", "slot_step_kernel"): {
         "src": "slot.hip", "src_sha": "2693a8a624b314e0", "bytes_per_launch": 94333359694},
     ("ring64_B_8MiB", "tree_step_kernel<reduce>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 283157990},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 283164468},
     ("ring64_B_8MiB", "tree_step_kernel<copy>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 207665478},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 207667846},
     ("ring8_B_32MiB", "tree_step_kernel<reduce>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 251701844},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 251707822},
     ("ring8_B_32MiB", "tree_step_kernel<copy>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 184596997},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 184599102},
     ("torus16x16x16_B_8MiB", "tree_step_kernel<reduce>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 9723961811},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 9724345370},
     ("torus16x16x16_B_8MiB", "tree_step_kernel<copy>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 6770476523},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 6770597524},
     ("torus32x32_B_8MiB", "tree_step_kernel<reduce>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 2286938665},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 2286992240},
     ("torus32x32_B_8MiB", "tree_step_kernel<copy>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 1679844735},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 1679865097},
     ("torus8x64_B_8MiB", "tree_step_kernel<reduce>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 1550511409},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 1550545718},
     ("torus8x64_B_8MiB", "tree_step_kernel<copy>"): {
-        "src": "executor.hip", "src_sha": "4fae51c83bf720a1", "bytes_per_launch": 1132502565},
+        "src": "executor.hip", "src_sha": "2aada099c9441419", "bytes_per_launch": 1132512386},
 }
 
 
@@ -438,6 +440,7 @@ def run_workload(w, steps, warmup, with_cpu, dtype="f32"):
         "roofline": roofline,
         "cpu_baseline": None,
     }
+    line["whole_call"] = whole_call(buf, plan, ws, regen, w.elems, first_cols, cols)
     if ws is not None:
         line["config"]["workspace_bytes"] = ws.numel()
     del buf, regen, ws
@@ -449,6 +452,40 @@ def run_workload(w, steps, warmup, with_cpu, dtype="f32"):
         _say(f"[bench] {w.name}: CPU oracle on {len(cols)} columns")
         line["cpu_baseline"] = cpu_baseline(w, first_cols, cols, V_cols)
     return line
+
+
+def whole_call(buf, plan, ws, regen, elems, first_cols, cols, reps=5):
+    """The same AllReduce through the whole-call form: mean time of `reps` calls on restored
+    inputs (HIP events around the call), the rate at which it reads and writes each vector once, and
+    whether the result has the step-by-step run's bits on the sampled columns."""
+    import torch
+
+    import paper_2602_17254_amd as T
+
+    stream = torch.cuda.current_stream()
+
+    def call():
+        if ws is None:
+            T.trivance_allreduce_emulated(buf, plan, stream)
+        else:
+            T.trivance_allreduce_emulated_ws(buf, plan, ws, stream)
+
+    ms = 0.0
+    for k in range(reps + 1):  # the first call is not timed
+        regen(stream)
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record(stream)
+        call()
+        e1.record(stream)
+        torch.cuda.synchronize()
+        ms += e0.elapsed_time(e1) / reps if k else 0.0
+    nbytes = 2 * plan.n * elems * 4
+    out = {"ms": round(ms, 4), "bytes": nbytes, "GBps": round(nbytes / (ms * 1e-3) / 1e9, 1)}
+    if first_cols is not None:
+        got = buf.index_select(1, torch.from_numpy(cols).cuda()).cpu().numpy()
+        out["same_bits_as_steps_on_sample"] = bool(
+            np.array_equal(got.view(np.uint32), first_cols.view(np.uint32)))
+    return out
 
 
 # The other named configurations of the metric, summarised inside the headline line.

@@ -60,6 +60,9 @@ CASES = [
     ((3, 27), 640_007, "f32", "schedule", 1, None),
     ((243,), 262_145, "f32", "natural", 0, None),
     ((32, 32), 65_537, "f32", "natural", 3, None),
+    # passes above 1 GiB, where the step kernels stream their stores
+    ((243,), 1_400_000, "f32", "natural", 0, None),
+    ((64,), 4_200_000, "f32", "natural", 0, None),
 ]
 
 

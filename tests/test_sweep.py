@@ -44,6 +44,8 @@ CASES = [
     ((8, 64), 4_102, "f32", 0, None), ((8, 8, 8), 5_001, "i32", 0, None),
     ((9, 9, 9), 7_003, "f32", 1, None), ((2, 3, 4), 129, "f32", 0, None),
     ((3, 3, 3, 3), 2_001, "f32", 0, None),
+    # passes above 1 GiB, where the step kernels stream their stores
+    ((81,), 1_700_000, "f32", 0, None), ((64,), 1_100_000, "f32", 0, None),
 ]
 
 

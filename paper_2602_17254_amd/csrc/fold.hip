@@ -17,7 +17,8 @@ namespace {
 
 // What the split and the layout rest on (MI355X, 16x16x16 ranks of 4 MiB unless said otherwise).
 // One read and one write of every vector at the rate of a plain copy (6.76 TB/s) take 5.08 ms; the
-// 18 step launches took 22.3 ms, fold and spread take 4.91.
+// 18 step launches took 22.4 ms, fold and spread take 4.98 (less than
+// the copy's: see the rates of pure reads and pure writes below).
 //  * Two launches. Waves that read their column of all rows and then write it to all rows drift
 //    apart, and with reads and writes of many rows mixed the memory gave 5.0-5.5 TB/s whatever
 //    the store policy, occupancy or batch. Reads alone reach 6.9-7.1, and one-store waves that
@@ -25,9 +26,10 @@ namespace {
 //    copies it. The one-launch form stays for calls below kSpreadBytes.
 //  * The scalar unit bounds the reads next: a wave's kibibyte may take 91 cycles of its compute
 //    unit, and decoding one row per program word took about as many. One word for the up to
-//    three rows of V(o, 1) cut the read part from 3.58 to 2.5 ms.
+//    three rows of V(o, 1) cut the read part from 3.58 to 2.69 ms.
 //  * Three nodes (up to nine loads) in flight per wave: two or four measured the same, six 18%
-//    slower (128 instead of 96 registers).
+//    slower (128 instead of 96 registers). Where several waves share a tile, five or six gained
+//    1% at 16x16x16 ranks of 64 Ki values and lost 27% at 64 ranks of 400000.
 constexpr int kFoldBatch = 3;
 constexpr int kStreamWaves = 4;  // tiles of a workgroup when a wave has a tile of its own
 

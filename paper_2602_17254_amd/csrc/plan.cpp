@@ -551,7 +551,7 @@ int trivance_plan_ex(int n, const int* torus_dims, int ndims, int variant, unsig
         try {
             rc = variant == TRIVANCE_BANDWIDTH_OPT ? build_tree_plan(p) : build_latency_slot_plan(p);
             if (rc == TRIVANCE_OK && variant == TRIVANCE_BANDWIDTH_OPT)
-                trivance::build_fold_programs(p, p->trees);
+                trivance::build_fold_programs(p);
             if (rc == TRIVANCE_OK && variant == TRIVANCE_LATENCY_OPT) trivance::build_sweep_programs(p);
         } catch (const std::bad_alloc&) {
             rc = TRIVANCE_ENOMEM;
@@ -588,14 +588,7 @@ int trivance_plan_ex(int n, const int* torus_dims, int ndims, int variant, unsig
                 p->passes.push_back(make_pass(p, *rot, TRIVANCE_PHASE_REDUCE_SCATTER, t));
             for (int t = p->S - 1; t >= 0; --t)
                 p->passes.push_back(make_pass(p, *rot, TRIVANCE_PHASE_ALLGATHER, t));
-            if (p->n <= trivance::kMaxFoldRanks) {
-                // on a power of three the tree of a dimension is the ordinary one
-                std::vector<trivance::DimTree> trees(p->D);
-                bool ok = true;
-                for (int d = 0; d < p->D; ++d)
-                    ok = ok && build_dim_tree(p->dims[d], &trees[d]) == TRIVANCE_OK;
-                if (ok) trivance::build_fold_programs(p, trees);
-            }
+            trivance::build_fold_programs(p);
         } else {
             for (int t = 0; t < p->S; ++t)
                 p->passes.push_back(make_pass(p, *rot, TRIVANCE_PHASE_LATENCY, t));

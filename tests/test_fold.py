@@ -31,6 +31,23 @@ def test_fold_programs_perform_the_schedules_adds(tmp_path):
     assert "0 failures" in res.stdout
 
 
+def test_plans_do_not_write_every_cut():
+    """The fold programs are written once per plan, for the cut chosen by counting. Best of 20 plans
+    (on a machine where these take 20 to 90 us; with a program written for every cut they took 750
+    to 1100 us): the bound lies a factor of three or more from both."""
+    import time
+
+    import paper_2602_17254_amd as T
+
+    for dims in ((6561,), (16, 18, 20), (10, 11, 12), (5, 6, 7, 8)):
+        best = 1.0
+        for _ in range(20):
+            t0 = time.perf_counter()
+            T.trivance_plan(dims, "B")
+            best = min(best, time.perf_counter() - t0)
+        assert best < 300e-6, f"{dims}: {best * 1e6:.0f} us"
+
+
 # (dims, elems, dtype, placement, elements the buffer starts beyond an aligned address, dispatch
 # limit). Small calls in local memory (one, two, four and eight cells to a thread), tiles of four and of sixteen waves at their narrowest and widest, a wave per tile, one launch
 # and two (192 MiB and more), a tail of 1 to 3 columns, segments of less than a tile, rows

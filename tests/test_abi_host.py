@@ -419,3 +419,19 @@ def test_missing_library_fails_loudly():
                          timeout=300)
     assert res.returncode == 0, res.stdout + res.stderr
     assert res.stdout.strip().endswith("raised")
+
+
+def test_current_stream_without_the_private_torch_calls():
+    """The binding's short way to the current stream's handle uses private torch calls; where torch
+    does not have them it takes the public one."""
+    from types import SimpleNamespace as NS
+
+    cuda = NS(current_stream=lambda: NS(cuda_stream=77))
+    both = NS(_cuda_getCurrentRawStream=lambda device: 100 + device, _cuda_getDevice=lambda: 3)
+    for private, want in ((both, 103), (NS(), 77), (NS(_cuda_getDevice=lambda: 3), 77)):
+        T.binding._TORCH = NS(_C=private, cuda=cuda)
+        try:
+            assert T.binding._stream_ptr(None) == want
+        finally:
+            T.binding._TORCH = None
+    assert T.binding._stream_ptr(NS(cuda_stream=5)) == 5 and T.binding._stream_ptr(6) == 6

@@ -3,6 +3,7 @@
 
 #include "calls.h"
 #include "device.h"
+#include "forms.h"
 #include "plan.h"
 
 namespace {
@@ -24,16 +25,14 @@ int check_call(void* buffers, int n, int64_t elems, int dtype, const trivance_pl
     return TRIVANCE_OK;
 }
 
-// A whole call: plans that a fold program (bandwidth-optimal, fold_plan.h) or a column program
-// (latency-optimal, sweep_plan.h) fits read and write each vector once, at every size faster than their
-// steps (measured from 1 KiB to 17 GB of vectors on 2 to 4096 ranks: 1.3 to 160 times); the others
-// run step by step.
 template <typename T>
 int run_whole(T* buf, int64_t elems, const trivance_plan_t* plan, T* ws, hipStream_t stream) {
-    if (trivance::tile_fits(plan, elems)) return trivance::run_tile_call(buf, elems, plan, stream);
-    if (trivance::fold_fits(plan, elems)) return trivance::run_fold_call(buf, elems, plan, stream);
-    if (trivance::sweep_fits(plan, elems))
-        return trivance::run_sweep_call(buf, elems, plan, stream);
+    switch (trivance::whole_form(plan, elems)) {
+        case trivance::Form::kTile: return trivance::run_tile_call(buf, elems, plan, stream);
+        case trivance::Form::kFold: return trivance::run_fold_call(buf, elems, plan, stream);
+        case trivance::Form::kSweep: return trivance::run_sweep_call(buf, elems, plan, stream);
+        default: break;
+    }
     return trivance::run_step_passes(buf, elems, plan, ws, stream, 0, (int)plan->passes.size());
 }
 

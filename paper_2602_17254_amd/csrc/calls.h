@@ -16,19 +16,16 @@ int run_step_passes(float* buf, int64_t elems, const trivance_plan_t* p, float* 
 int run_step_passes(int* buf, int64_t elems, const trivance_plan_t* p, int* ws, hipStream_t stream,
                     int pb, int pe);
 
-// Whole bandwidth-optimal calls, each vector read once and written once (fold.hip): whether plan
-// and size allow it, and the call.
-bool fold_fits(const trivance_plan_t* p, int64_t elems);
+// Whole bandwidth-optimal calls, each vector read once and written once (fold.hip). Which plans and sizes
+// these and the forms below take: whole_form (forms.h).
 int run_fold_call(float* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream);
 int run_fold_call(int* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream);
 
 // Small ones of these in tiles of local memory (tile.hip).
-bool tile_fits(const trivance_plan_t* p, int64_t elems);
 int run_tile_call(float* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream);
 int run_tile_call(int* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream);
 
 // The same for whole latency-optimal calls (sweep.hip).
-bool sweep_fits(const trivance_plan_t* p, int64_t elems);
 int run_sweep_call(float* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream);
 int run_sweep_call(int* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream);
 

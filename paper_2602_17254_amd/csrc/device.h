@@ -161,8 +161,6 @@ __device__ __forceinline__ uint32_t xcd_contiguous(uint32_t wg, uint32_t nwg) {
     return xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
 }
 
-constexpr uint32_t kComputeUnits = 256;
-
 // Where and how a call's launches go: the stream, and the most work-items of one dispatch (the
 // plan's limit).
 struct Exec {

@@ -10,6 +10,7 @@
 
 #include "calls.h"
 #include "device.h"
+#include "forms.h"
 #include "plan.h"
 
 namespace trivance {
@@ -31,7 +32,6 @@ namespace {
 //    slower (128 instead of 96 registers). Where several waves share a tile, five or six gained
 //    1% at 16x16x16 ranks of 64 Ki values and lost 27% at 64 ranks of 400000.
 constexpr int kFoldBatch = 3;
-constexpr int kStreamWaves = 4;  // tiles of a workgroup when a wave has a tile of its own
 
 struct FoldArgs {
     int64_t elems;
@@ -288,7 +288,6 @@ struct SpreadArgs {
     uint32_t wg_base;
     int shifted;
 };
-constexpr uint32_t kSpreadTile = 256;  // elements of one wave
 constexpr uint32_t kSpreadPanel = 4096;
 constexpr int kSpreadWaves = 4;
 
@@ -345,52 +344,6 @@ hipError_t launch_spread(T* buf, int64_t elems, const trivance_plan_t* p, const 
     return err;
 }
 
-struct FoldShape {
-    int spread;      // 1: result to row 0, spread_kernel copies it
-    int waves;       // waves per tile
-    uint32_t lanes;  // column vectors of a tile
-};
-
-size_t fold_lds(const FoldShape& s, size_t roots, int sub_depth, int top_depth) {
-    if (s.waves == 1) return (size_t)kStreamWaves * (sub_depth + top_depth) * 64 * 16;
-    return (roots + 1 + (size_t)s.waves * sub_depth + top_depth) * s.lanes * 16;
-}
-
-// Fold and spread from 192 MiB of vectors on. Measured in us, one launch against two, at 134 MB
-// (ring of 8) 45.7 / 46.3, at 191 MB (27x27) 68.4 / 65.9, at 255 MB (ring of 243) 88 / 81, at 268 MB
-// (rings of 4 and 64) 91 / 81 and 92 / 82: below the size of the 256 MB last-level cache the writes
-// of the one launch end there, and the second launch costs 3 us.
-constexpr int64_t kSpreadBytes = (int64_t)192 << 20;
-// A wave per tile from 2048 tiles of 1 KiB on (524,288 elements): it needs no local memory for the
-// subtrees and no barrier. With fewer tiles that leaves compute units idle, so sixteen waves share
-// one. In us, sixteen waves against one: 32x32 ranks at 524,288 elements 717 / 631, at 262,144
-// 364 / 427, at 65,536 97 / 298; 16x16x16 at 524,288 3576 / 2743, at 262,144 1852 / 1957; 27x27 at
-// 16,384 23 / 168.
-constexpr int64_t kStreamVecs = (int64_t)2048 * 64;
-// With at most eight subtrees four waves share a tile (more would find none). Tiles narrow down
-// to 64 bytes while there are fewer than one per compute unit: 27x27 ranks of 4096 elements 26
-// us with 1 KiB tiles, 20 with 256 B and 19 with 64 B.
-// Local memory of a tile's subtrees: all of a compute unit's if need be. 32x32 ranks of 65,536
-// elements took 117 us with tiles narrowed to fit 64 KiB and 97 with 156 KiB.
-constexpr size_t kFoldLds = 156 * 1024;
-
-inline FoldShape fold_shape(const trivance_plan_t* p, int64_t elems) {
-    size_t roots = 0;
-    int sub_depth = 0, top_depth = 0;
-    for (const FoldProgram& f : p->folds) {
-        roots = std::max(roots, f.roots.size());
-        sub_depth = std::max(sub_depth, f.sub_depth);
-        top_depth = std::max(top_depth, f.top_depth);
-    }
-    const int64_t vecs = (elems + 3) / 4;
-    FoldShape s{(int64_t)p->n * elems * 4 >= kSpreadBytes ? 1 : 0, 1, 64};
-    if (vecs >= kStreamVecs) return s;
-    s.waves = roots > 8 ? 16 : 4;
-    while (s.lanes > 4 && vecs < (int64_t)kComputeUnits * s.lanes) s.lanes /= 2;
-    while (s.lanes > 4 && fold_lds(s, roots, sub_depth, top_depth) > kFoldLds) s.lanes /= 2;
-    return s;
-}
-
 template <typename T, int D, int P>
 hipError_t launch_fold(T* buf, FoldArgs a, uint64_t grid, size_t lds, const Exec& x) {
     hipError_t err = hipSuccess;
@@ -431,9 +384,7 @@ int run_fold_dims(T* buf, int64_t elems, const trivance_plan_t* p, hipStream_t s
     }
     a.narrow = (int64_t)p->n * (max_gc + 1) < ((int64_t)1 << 31) ? 1 : 0;
     // programs: all in one launch, or one launch per collective
-    size_t words = 0;
-    for (const FoldProgram& f : p->folds) words += f.words();
-    const bool together = words <= kMaxFoldWords;
+    const bool together = fold_together(p);
     for (int c0 = 0; c0 < D; c0 += together ? D : 1) {
         const int c1 = together ? D : c0 + 1;
         uint32_t used = 0;
@@ -495,11 +446,6 @@ int run_fold(T* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream
 }
 
 }  // namespace
-
-bool fold_fits(const trivance_plan_t* p, int64_t elems) {
-    return !p->folds.empty() && elems < ((int64_t)1 << 28) &&
-           (int64_t)p->n * ((elems + kSpreadTile - 1) / kSpreadTile + 1) < ((int64_t)1 << 31) - 4;
-}
 
 int run_fold_call(float* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream) {
     return run_fold(buf, elems, p, stream);

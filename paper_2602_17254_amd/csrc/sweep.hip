@@ -9,6 +9,7 @@
 
 #include "calls.h"
 #include "device.h"
+#include "forms.h"
 #include "plan.h"
 
 namespace trivance {
@@ -24,7 +25,7 @@ struct alignas(16) SweepOp {
     uint32_t dst;
     uint32_t by[3][H];
     uint32_t pad[4 - 3 * H % 4];
-    static constexpr uint32_t kWords = 8 + (H > 1 ? 4 : 0);
+    static constexpr uint32_t kWords = sweep_op_words(D);
 };
 constexpr uint32_t kTwoTerms = 1u;   // no third term
 constexpr uint32_t kLevelEnd = 2u;   // last operation of its level
@@ -34,7 +35,6 @@ typedef unsigned short U16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t U32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ U16x2 as_u16x2(uint32_t w) { return __builtin_bit_cast(U16x2, w); }
 
-constexpr uint32_t kSweepTabWords = 896;
 struct SweepArgs {
     int64_t elems;
     int64_t seg_g[kMaxSweepDims + 1];
@@ -247,57 +247,6 @@ void sweep_kernel(T* __restrict__ buf, SweepArgs a) {
     } while (LOOP);
 }
 
-// Tile and thread counts, measured over the plans and sizes of the tests and benchmarks:
-//  * up to 64 column vectors, while at least four workgroups fit a compute unit (three up to four
-//    vectors, 64 bytes of a row): ring of 81 with 16 vectors 263 us, 32 273, 8 279; ring of 729 with
-//    four 389, two 537.
-//  * four cells to a thread from 1024 cells on for one operation a level (ring of 81: four 263, two
-//    283, one 407; of 27: two 164, four 167), two with up to four operations (ring of 64: two 265, one
-//    376), one where fewer than three workgroups fit (32x32: one 665, two 782).
-//  * fewer vectors to a tile while there is less than a tile per compute unit.
-struct SweepShape {
-    uint32_t shift;  // column vectors of a tile: 1 << shift
-    int cells;       // per thread
-    int ops;         // operations of a level, rounded up to a compiled size
-    int threads;
-    size_t lds;
-    uint32_t per_cu;  // workgroups a compute unit runs
-};
-
-constexpr size_t kSweepLds = 160 * 1024 - 256;
-
-bool sweep_shape(const trivance_plan_t* p, int64_t elems, SweepShape* s) {
-    // one step of powers of three: a read and a write as well (ring of 3: step 63 us, tile 74)
-    if (p->sweeps.empty() || (p->S == 1 && p->slots.empty())) return false;
-    int ops = 0, slots = 0;
-    size_t words = 1;
-    for (int c = 0; c < p->D; ++c) {
-        const SweepProgram& g = p->sweeps[p->sweeps.size() == 1 ? 0 : c];
-        ops = std::max(ops, g.max_ops);
-        slots = std::max(slots, g.slots);
-        words += g.words.size() / 4;
-    }
-    if (ops > 12 || words * (p->D <= 2 ? SweepOp<2>::kWords : SweepOp<4>::kWords) > kSweepTabWords)
-        return false;
-    s->ops = ops == 1 ? 1 : (ops <= 4 ? 4 : 12);
-    const size_t col = (size_t)slots * p->n * 16;  // local memory per column vector
-    const int64_t vecs = (elems + 3) / 4;
-    const int most = s->ops == 1 ? 4 : (s->ops == 4 ? 2 : 1);
-    s->shift = 0;
-    while (s->shift < 6 && ((int64_t)p->n << (s->shift + 1)) <= 1024 * most &&
-           (col << (s->shift + 1)) <= (s->shift < 2 ? kSweepLds / 3 : kSweepLds / 4))
-        ++s->shift;
-    while (s->shift > 0 && vecs < (int64_t)kComputeUnits << s->shift) --s->shift;
-    const int64_t cells = (int64_t)p->n << s->shift;
-    s->cells = s->ops == 1 ? (cells > 1024 ? 4 : 2) : s->ops == 4 && cells <= 1024 ? 2 : most;
-    if (s->ops > 1 && 3 * (col << s->shift) > kSweepLds && cells <= 1024) s->cells = 1;
-    s->threads = (int)((cells + 64 * s->cells - 1) / (64 * s->cells)) * 64;
-    s->lds = col << s->shift;
-    if (s->lds > kSweepLds || s->threads > 1024 || s->cells > most || cells > 32767) return false;
-    s->per_cu = (uint32_t)std::min<size_t>(kSweepLds / s->lds, 2048 / s->threads);
-    return true;
-}
-
 template <typename T, int D, int CELLS, int OPS, bool LOOP>
 hipError_t launch_sweep(T* buf, SweepArgs a, const SweepShape& s, const Exec& x) {
     hipError_t err = hipSuccess;
@@ -358,8 +307,7 @@ int run_sweep_dims(T* buf, int64_t elems, const trivance_plan_t* p, hipStream_t 
         tiles += (uint32_t)(((len + 3) / 4 + ((int64_t)1 << s.shift) - 1) >> s.shift);
         a.tile_end[c] = tiles;
     }
-    a.grid = s.per_cu > 2 || s.cells > 1 || s.ops == 1 ? tiles
-                                                       : std::min(tiles, kComputeUnits * s.per_cu);
+    a.grid = sweep_grid(s, tiles);
     hipError_t err = hipErrorInvalidValue;
     const bool loop = a.grid < tiles;
     if (s.ops == 1) {
@@ -390,11 +338,6 @@ int run_sweep(T* buf, int64_t elems, const trivance_plan_t* p, hipStream_t strea
 }
 
 }  // namespace
-
-bool sweep_fits(const trivance_plan_t* p, int64_t elems) {
-    SweepShape s;
-    return elems < ((int64_t)1 << 32) && sweep_shape(p, elems, &s);
-}
 
 int run_sweep_call(float* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream) {
     return run_sweep(buf, elems, p, stream);

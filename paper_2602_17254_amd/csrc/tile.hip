@@ -10,6 +10,7 @@
 
 #include "calls.h"
 #include "device.h"
+#include "forms.h"
 #include "plan.h"
 
 namespace trivance {
@@ -170,37 +171,6 @@ __global__ __launch_bounds__(1024) void tile_kernel(T* __restrict__ buf, TileArg
     }
 }
 
-struct TileShape {
-    uint32_t shift;
-    int cells;  // per thread
-    int threads;
-};
-
-// Up to 24 MiB of vectors or 4096 values a rank. In us, fold.hip's waves against these tiles: 27x27
-// ranks of 256 values 18 / 6, of 4096 (12 MB) 19 / 10, of 16,384 (48 MB) 23 / 40; 16x16x16 of 256
-// values 107 / 22, of 4096 (67 MB) 129 / 84, of 16,384 174 / 536; rings of 64 and 243 equal at 17 MB.
-// Below, a row is in flight from every thread at once and a step costs 0.4 us; above, the fold
-// reads longer pieces of a row.
-constexpr int64_t kTileBytes = (int64_t)24 << 20;
-constexpr int64_t kTileElems = 4096;
-
-bool tile_shape(const trivance_plan_t* p, int64_t elems, TileShape* s) {
-    if (p->tile_masks.empty()) return false;
-    if ((int64_t)p->n * elems * 4 > kTileBytes && elems > kTileElems) return false;
-    // as many vectors to a tile as leave two tiles for every compute unit (27x27 ranks of 256
-    // values: one 6.2 us, two 7.7, four 10.8; of 4096: one 11.7, two 9.6, four 12.2)
-    const int64_t vecs = (elems + 3) / 4, most = std::max(2048, 2 * p->n);
-    s->shift = 0;
-    while (s->shift < 6 && vecs >= 2 * (int64_t)kComputeUnits << (s->shift + 1) &&
-           ((int64_t)p->n << (s->shift + 1)) <= most)
-        ++s->shift;
-    const int64_t cells = (int64_t)p->n << s->shift;
-    s->cells = 1;
-    while (s->cells < 8 && cells > 1024 * s->cells) s->cells *= 2;
-    s->threads = (int)((cells + 64 * s->cells - 1) / (64 * s->cells)) * 64;
-    return cells * 16 <= 159 * 1024 && s->threads <= 1024;
-}
-
 template <typename T, int D, int CELLS>
 hipError_t launch_tile(T* buf, TileArgs a, uint32_t grid, int threads, const Exec& x) {
     hipError_t err = hipSuccess;
@@ -268,11 +238,6 @@ int run_tile(T* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream
 }
 
 }  // namespace
-
-bool tile_fits(const trivance_plan_t* p, int64_t elems) {
-    TileShape s;
-    return elems < ((int64_t)1 << 28) && tile_shape(p, elems, &s);
-}
 
 int run_tile_call(float* buf, int64_t elems, const trivance_plan_t* p, hipStream_t stream) {
     return run_tile(buf, elems, p, stream);

@@ -1,6 +1,10 @@
-"""Helpers of the GPU parity tests: run the HIP path, run the oracle, compare."""
+"""Helpers of the GPU parity tests: run the HIP path, run the oracle, compare; and which form runs a
+call."""
 
 from __future__ import annotations
+
+import os
+import subprocess
 
 import numpy as np
 
@@ -122,3 +126,19 @@ def placement_labels(E: int, dims, cols=None):
     from oracle import placement
 
     return placement.column_labels(E, dims, cols)
+
+
+def forms(tmp_path, calls):
+    """Form and launch shape of whole calls (variant, dims, placement, elems), a line each as
+    tests/c/forms.cpp prints them."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    csrc = os.path.join(root, "paper_2602_17254_amd", "csrc")
+    exe = str(tmp_path / "forms")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", csrc,
+                    os.path.join(root, "tests", "c", "forms.cpp"), os.path.join(csrc, "plan.cpp"),
+                    "-o", exe], check=True)
+    args = []
+    for variant, dims, placement, elems in calls:
+        args += [variant, "x".join(map(str, dims)), placement, str(elems)]
+    res = subprocess.run([exe, *args], capture_output=True, text=True, check=True, timeout=60)
+    return res.stdout.splitlines()

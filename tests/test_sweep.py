@@ -2,8 +2,8 @@
 
 CPU: every column program performs the steps' own adds (tests/c/sweep_program.cpp, plan.cpp built
 with g++). GPU: the whole call gives the same bits as the same plan run one pass at a time through
-trivance_allreduce_emulated_steps_ws, on every shape the launcher distinguishes; the other GPU
-tests compare the whole call with the oracle."""
+trivance_allreduce_emulated_steps_ws, on every launch form that forms.h distinguishes (checked on the
+host); other GPU tests compare the whole call and the steps with the oracle."""
 
 import os
 import shutil
@@ -11,6 +11,8 @@ import subprocess
 
 import numpy as np
 import pytest
+
+from gpu_util import forms
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2602_17254_amd", "csrc")
@@ -30,23 +32,52 @@ def test_column_programs_perform_the_schedules_adds(tmp_path):
     assert "0 failures" in res.stdout
 
 
-# (dims, elems, dtype, elements the buffer starts beyond an aligned address, dispatch limit): one, up
-# to four and up to twelve operations a level; one, two and four cells to a thread; one tile and
-# several to a workgroup; the widest and narrowest tiles, columns that end inside a vector and a
-# segment of less than a tile; one to four dimensions; launches split over several dispatches.
+# (dims, elems, dtype, elements the buffer starts beyond an aligned address, dispatch limit, form and
+# launch shape as tests/c/forms.cpp prints them): one, up to four and up to twelve operations a level;
+# one, two and four cells to a thread; one tile and several to a workgroup; the widest and narrowest
+# tiles, columns that end inside a vector and a segment of less than a tile; one to four dimensions;
+# launches split over several dispatches.
 CASES = [
-    ((2,), 1001, "f32", 0, None), ((3,), 4099, "f32", 1, None), ((5,), 3, "f32", 0, None),
-    ((8,), 70_001, "i32", 3, None), ((9,), 70_003, "f32", 0, 1024), ((27,), 33_000, "f32", 0, None),
-    ((64,), 20_002, "f32", 2, 1024), ((81,), 40_001, "i32", 0, None), ((243,), 9_001, "f32", 0, None),
-    ((300,), 5_003, "f32", 1, None), ((729,), 4_099, "f32", 0, None), ((1, 9), 1001, "f32", 0, None),
-    ((9, 9), 26_215, "i32", 1, None), ((5, 7), 3_001, "f32", 0, None),
-    ((16, 16), 9_001, "f32", 0, 65536), ((32, 32), 4_101, "f32", 3, None),
-    ((8, 64), 4_102, "f32", 0, None), ((8, 8, 8), 5_001, "i32", 0, None),
-    ((9, 9, 9), 7_003, "f32", 1, None), ((2, 3, 4), 129, "f32", 0, None),
-    ((3, 3, 3, 3), 2_001, "f32", 0, None),
+    ((2,), 1001, "f32", 0, None, "sweep o1 c2 v1"),
+    ((3,), 4099, "f32", 1, None, "steps"),
+    ((5,), 3, "f32", 0, None, "sweep o1 c2 v1"),
+    ((8,), 70_001, "i32", 3, None, "sweep o4 c2 v64"),
+    ((9,), 70_003, "f32", 0, 1024, "sweep o1 c2 v64"),
+    ((27,), 33_000, "f32", 0, None, "sweep o1 c2 v32"),
+    ((64,), 20_002, "f32", 2, 1024, "sweep o4 c2 v8"),
+    ((81,), 40_001, "i32", 0, None, "sweep o1 c4 v16"),
+    ((243,), 9001, "f32", 0, None, "sweep o1 c4 v8"),
+    ((300,), 5003, "f32", 1, None, "sweep o4 c2 v2"),
+    ((729,), 4099, "f32", 0, None, "sweep o1 c4 v4"),
+    ((1, 9), 1001, "f32", 0, None, "sweep o1 c2 v1"),
+    ((9, 9), 26_215, "i32", 1, None, "sweep o1 c4 v16"),
+    ((5, 7), 3001, "f32", 0, None, "sweep o12 c1 v2"),
+    ((16, 16), 9001, "f32", 0, 1 << 16, "sweep o12 c1 v1"),
+    ((32, 32), 4101, "f32", 3, None, "sweep o4 c1 v1 loop"),
+    ((8, 64), 4102, "f32", 0, None, "sweep o12 c1 v1 loop"),
+    ((8, 8, 8), 5001, "i32", 0, None, "sweep o12 c1 v1 loop"),
+    ((9, 9, 9), 7003, "f32", 1, None, "sweep o1 c4 v4"),
+    ((2, 3, 4), 129, "f32", 0, None, "sweep o4 c2 v1"),
+    ((3, 3, 3, 3), 2001, "f32", 0, None, "sweep o1 c2 v1"),
+    ((32, 32), 500, "f32", 0, None, "sweep o4 c1 v1"),
+    ((27, 81), 1030, "i32", 0, None, "sweep o1 c4 v1"),
+    ((2000,), 1001, "f32", 0, 1024, "sweep o4 c2 v1"),
+    ((2, 2, 2, 2), 1001, "f32", 0, None, "sweep o1 c2 v1"),
+    ((4, 7), 20, "f32", 0, None, "sweep o12 c1 v1"),
     # passes above 1 GiB, where the step kernels stream their stores
-    ((81,), 1_700_000, "f32", 0, None), ((64,), 1_100_000, "f32", 0, None),
+    ((81,), 1_700_000, "f32", 0, None, "sweep o1 c4 v16"),
+    ((64,), 1_100_000, "f32", 0, None, "sweep o4 c2 v8"),
 ]
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not found")
+def test_cases_reach_every_form(tmp_path):
+    """The forms that the cases name are the ones that run them, and they meet every compiled kernel
+    of sweep.hip."""
+    assert forms(tmp_path, [("L", c[0], "natural", c[1]) for c in CASES]) == [c[5] for c in CASES]
+    seen = {f.rsplit(" v", 1)[0] + (" loop" if "loop" in f else "") for *_, f in CASES}
+    assert seen == {"steps", "sweep o1 c2", "sweep o1 c4", "sweep o4 c2", "sweep o4 c1",
+                    "sweep o4 c1 loop", "sweep o12 c1", "sweep o12 c1 loop"}
 
 
 @pytest.mark.gpu
@@ -57,7 +88,7 @@ def test_whole_call_equals_the_steps(case):
 
     import paper_2602_17254_amd as T
 
-    dims, E, dtype, offset, limit = case
+    dims, E, dtype, offset, limit, _ = case
     n = int(np.prod(dims))
     print(f"[sweep] {case}", flush=True)
     plan = T.trivance_plan(dims, "L")

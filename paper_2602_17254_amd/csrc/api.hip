@@ -27,7 +27,7 @@ int check_call(void* buffers, int n, int64_t elems, int dtype, const trivance_pl
 
 template <typename T>
 int run_whole(T* buf, int64_t elems, const trivance_plan_t* plan, T* ws, hipStream_t stream) {
-    switch (trivance::whole_form(plan, elems)) {
+    switch (trivance::whole_form(plan, elems, (uintptr_t)buf % 16 == 0)) {
         case trivance::Form::kTile: return trivance::run_tile_call(buf, elems, plan, stream);
         case trivance::Form::kFold: return trivance::run_fold_call(buf, elems, plan, stream);
         case trivance::Form::kSweep: return trivance::run_sweep_call(buf, elems, plan, stream);

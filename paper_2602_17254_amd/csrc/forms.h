@@ -176,23 +176,33 @@ inline uint32_t sweep_grid(const SweepShape& s, uint32_t tiles) {
     return std::min(tiles, kComputeUnits * s.per_cu);
 }
 
-inline bool sweep_fits(const trivance_plan_t* p, int64_t elems) {
+// Tiles of 16 bytes of a row (2187 ranks) read every cache line eight times, and rows a multiple of 2 MiB
+// apart share their cache sets, so that few lines last until the next tile comes. On powers of three the
+// steps are the faster form then, unless they would run on single elements (`aligned` 0: the vectors
+// do not start at 16 bytes). In us, sweep / steps: 9x9x27 ranks of 524,288 values 13375 / 10495, of
+// 1,048,576 26448 / 20881, ring of 2187 12719 / 11187 and 25182 / 22835; of 786,432 values 14635 / 15240
+// and 13929 / 17049, of 524,320 6153 / 10602 and 5569 / 11535; 9x9x27 of 524,288 unaligned 14252 / 27740.
+// Plans with several operations a level carry partial sums through memory in their steps and stay
+// faster here (1944 ranks of 524,288 values 11906 / 19718, 2000 14304 / 35021).
+constexpr int64_t kAliasElems = (int64_t)1 << 19;
+
+inline bool sweep_fits(const trivance_plan_t* p, int64_t elems, bool aligned) {
     SweepShape s;
-    return elems < ((int64_t)1 << 32) && sweep_shape(p, elems, &s);
+    if (elems >= ((int64_t)1 << 32) || !sweep_shape(p, elems, &s)) return false;
+    return !(aligned && s.ops == 1 && s.shift == 0 && elems % kAliasElems == 0);
 }
 
 // ---- the choice ----
 
 // A whole call: plans that a fold program (bandwidth-optimal, fold_plan.h) or a column program
-// (latency-optimal, sweep_plan.h) fits read and write each vector once, at every size faster than their
-// steps (measured from 1 KiB to 17 GB of vectors on 2 to 4096 ranks: 1.3 to 160 times); the others
-// run step by step.
+// (latency-optimal, sweep_plan.h) fits read and write each vector once; the others run step by step.
+// `aligned`: the vectors start at a multiple of 16 bytes.
 enum class Form { kTile, kFold, kSweep, kSteps };
 
-inline Form whole_form(const trivance_plan_t* p, int64_t elems) {
+inline Form whole_form(const trivance_plan_t* p, int64_t elems, bool aligned) {
     if (tile_fits(p, elems)) return Form::kTile;
     if (fold_fits(p, elems)) return Form::kFold;
-    if (sweep_fits(p, elems)) return Form::kSweep;
+    if (sweep_fits(p, elems, aligned)) return Form::kSweep;
     return Form::kSteps;
 }
 

@@ -1,6 +1,7 @@
 // The form that runs a whole AllReduce call and its launch shape, as the rules of forms.h give them.
 // Built with g++ against plan.cpp; no GPU. One line of output per call:
 //   forms VARIANT SIDES PLACEMENT ELEMS [VARIANT SIDES PLACEMENT ELEMS ...]    (B 27x27 natural 4098 ...)
+// with ELEMS+K for vectors that start K elements beyond a multiple of 16 bytes:
 //     tile c<cells of a thread> v<vectors of a tile>
 //     fold w<waves of a tile> v<vectors of a tile> one|spread [per-collective]
 //     sweep o<operations of a level> c<cells of a thread> v<vectors of a tile> [loop]
@@ -34,12 +35,14 @@ int main(int argc, char** argv) {
             s = *end ? end + 1 : end;
         }
         const int64_t elems = std::strtoll(argv[i + 3], nullptr, 10);
+        const char* plus = std::strchr(argv[i + 3], '+');
+        const bool aligned = !plus || std::atoi(plus + 1) % 4 == 0;
         trivance_plan_t* p = nullptr;
         if (trivance_plan_ex(n, dims, D, *argv[i] == 'L' ? TRIVANCE_LATENCY_OPT : TRIVANCE_BANDWIDTH_OPT,
                              std::strcmp(argv[i + 2], "natural") ? TRIVANCE_PLACE_BY_SCHEDULE : 0u,
                              &p) != TRIVANCE_OK)
             return 1;
-        switch (whole_form(p, elems)) {
+        switch (whole_form(p, elems, aligned)) {
             case Form::kTile: {
                 TileShape s{};
                 tile_shape(p, elems, &s);

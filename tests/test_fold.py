@@ -104,7 +104,7 @@ CASES = [
 def test_cases_reach_every_form(tmp_path):
     """The forms that the cases name are the ones that run them, so that a limit that moves later
     takes no case along unseen; and the cases meet every compiled kernel of tile.hip and fold.hip."""
-    assert forms(tmp_path, [("B", c[0], c[3], c[1]) for c in CASES]) == [c[6] for c in CASES]
+    assert forms(tmp_path, [("B", c[0], c[3], f"{c[1]}+{c[4]}") for c in CASES]) == [c[6] for c in CASES]
     seen = {c[6] for c in CASES}
     assert {f.split(" v")[0] for f in seen if f.startswith("tile")} == {f"tile c{c}" for c in (1, 2, 4, 8)}
     for waves in (1, 4, 16):

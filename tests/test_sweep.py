@@ -74,10 +74,22 @@ CASES = [
 def test_cases_reach_every_form(tmp_path):
     """The forms that the cases name are the ones that run them, and they meet every compiled kernel
     of sweep.hip."""
-    assert forms(tmp_path, [("L", c[0], "natural", c[1]) for c in CASES]) == [c[5] for c in CASES]
+    assert forms(tmp_path, [("L", c[0], "natural", f"{c[1]}+{c[3]}") for c in CASES]) == [c[5] for c in CASES]
     seen = {f.rsplit(" v", 1)[0] + (" loop" if "loop" in f else "") for *_, f in CASES}
     assert seen == {"steps", "sweep o1 c2", "sweep o1 c4", "sweep o4 c2", "sweep o4 c1",
                     "sweep o4 c1 loop", "sweep o12 c1", "sweep o12 c1 loop"}
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not found")
+def test_narrow_tiles_on_aliased_rows_run_step_by_step(tmp_path):
+    """2187 ranks leave tiles of 16 bytes, which lose to the steps on rows a multiple of 2 MiB apart:
+    only there, on powers of three, and where the steps run on 16-byte vectors."""
+    calls = [((27, 81), 1 << 19), ((2187,), 3 << 19), ((9, 9, 9, 3), 1 << 20),  # the steps' side
+             ((27, 81), (1 << 19) + 4), ((27, 81), 3 << 18), ((27, 81), f"{1 << 19}+1"),
+             ((27, 27), 1 << 19), ((8, 9, 27), 1 << 19)]
+    got = forms(tmp_path, [("L", dims, "natural", E) for dims, E in calls])
+    assert got[:3] == ["steps"] * 3
+    assert [f.split(" ")[0] for f in got[3:]] == ["sweep"] * 5
 
 
 @pytest.mark.gpu

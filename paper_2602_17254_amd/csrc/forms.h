@@ -71,6 +71,18 @@ inline size_t fold_lds(const FoldShape& s, size_t roots, int sub_depth, int top_
 // (rings of 4 and 64) 91 / 81 and 92 / 82: below the size of the 256 MB last-level cache the writes
 // of the one launch end there, and the second launch costs 3 us.
 constexpr int64_t kSpreadBytes = (int64_t)192 << 20;
+// Not on two ranks, nor on three whose rows exceed that cache: the second launch reads row 0 once more,
+// a fourth or a sixth on top of the call's traffic, and two launches were slower than the steps. In
+// us over three sets of vectors in turn, two launches / steps / one: 2 ranks at 403 MB 143 / 141 / 130,
+// at 1600 MB 611 / 598 / 509; 3 ranks at 403 MB 136 / 140 / 145, at 2400 MB 871 / 869 / 815 (as a
+// torus of 1x3 887 / 869 / 799); 4 ranks at 2400 MB 848 / 1357 / 838.
+constexpr int64_t kLastLevelBytes = (int64_t)256 << 20;
+
+inline bool fold_spreads(int n, int64_t elems) {
+    if (n * elems * 4 < kSpreadBytes || n == 2) return false;
+    return n > 3 || elems * 4 <= kLastLevelBytes;
+}
+
 // A wave per tile from 2048 tiles of 1 KiB on (524,288 elements): it needs no local memory for the
 // subtrees and no barrier. With fewer tiles that leaves compute units idle, so sixteen waves share
 // one. In us, sixteen waves against one: 32x32 ranks at 524,288 elements 717 / 631, at 262,144
@@ -90,7 +102,7 @@ inline FoldShape fold_shape(const trivance_plan_t* p, int64_t elems) {
         top_depth = std::max(top_depth, f.top_depth);
     }
     const int64_t vecs = (elems + 3) / 4;
-    FoldShape s{(int64_t)p->n * elems * 4 >= kSpreadBytes ? 1 : 0, 1, 64};
+    FoldShape s{fold_spreads(p->n, elems) ? 1 : 0, 1, 64};
     if (vecs >= kStreamVecs) return s;
     // with at most eight subtrees four waves share a tile (more would find none)
     s.waves = roots > 8 ? 16 : 4;

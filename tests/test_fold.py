@@ -94,6 +94,7 @@ CASES = [
     ((10, 11, 12), 50_003, "i32", "natural", 1, None, "fold w16 v32 spread per-collective"),
     ((10, 11, 12), 540_002, "f32", "natural", 0, None, "fold w1 v64 spread per-collective"),
     ((5, 6, 7, 8), 4500, "f32", "natural", 0, None, "fold w16 v4 one per-collective"),
+    ((2,), 26_000_002, "f32", "natural", 1, None, "fold w1 v64 one"),
     # passes above 1 GiB, where the step kernels stream their stores
     ((243,), 1_400_000, "f32", "natural", 0, None, "fold w1 v64 spread"),
     ((64,), 4_200_000, "f32", "natural", 0, None, "fold w1 v64 spread"),
@@ -114,6 +115,17 @@ def test_cases_reach_every_form(tmp_path):
         assert any(f.startswith(f"fold w{waves} ") and "per-collective" in f for f in seen)
     # tiles at their narrowest and widest
     assert {"fold w4 v32 one", "fold w4 v64 one", "fold w16 v4 one", "fold w16 v64 spread"} <= seen
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not found")
+def test_two_and_three_ranks_spread_only_from_cached_rows(tmp_path):
+    """On two ranks, and on three whose rows exceed the last-level cache, fold and spread lose to
+    the steps; one launch does not."""
+    row = 1 << 26  # elements that fill the 256 MiB cache
+    calls = [((2,), row // 2), ((2,), 3 * row), ((2, 1), row), ((3,), row + 1), ((1, 3), 2 * row),
+             ((3,), row), ((3,), 17_000_000), ((4,), 2 * row), ((2, 2), row)]
+    got = forms(tmp_path, [("B", dims, "natural", E) for dims, E in calls])
+    assert got == ["fold w1 v64 one"] * 5 + ["fold w1 v64 spread"] * 4
 
 
 @pytest.mark.gpu

@@ -37,7 +37,6 @@ struct FoldArgs {
     int64_t elems;
     int64_t seg_g[kMaxFoldDims + 1];
     uint32_t n;
-    int narrow;                          // 1 if n * (granules of a segment + 1) < 2^31
     uint32_t side[kMaxFoldDims], stride[kMaxFoldDims];
     FastDiv32 f_side[kMaxFoldDims];
     FastDiv32 f_gc[kMaxFoldDims];        // granules of segment c
@@ -82,12 +81,7 @@ __device__ __forceinline__ void fold_tile(T* __restrict__ buf, const FoldArgs& a
 
     // the block of this lane's columns and its coordinates
     const uint32_t gr = (uint32_t)((col0 - seg_b + (int64_t)cl * VEC) / kGranule);
-    uint32_t j;
-    if (a.narrow) {
-        j = fdiv32((gr + 1) * a.n - 1, a.f_gc[c]);
-    } else {
-        j = (uint32_t)(((uint64_t)(gr + 1) * a.n - 1) / (uint64_t)(a.seg_g[c + 1] - a.seg_g[c]));
-    }
+    uint32_t j = fdiv32((gr + 1) * a.n - 1, a.f_gc[c]);
     uint32_t y[D] = {};
     if (a.placed) {
         // j is the block's position: its base-3 digits, the last step's lowest
@@ -371,10 +365,8 @@ int run_fold_dims(T* buf, int64_t elems, const trivance_plan_t* p, hipStream_t s
     a.placed = p->placed ? 1 : 0;
     a.steps = (uint32_t)p->S;
     const int64_t G = (elems + kGranule - 1) / kGranule;
-    int64_t max_gc = 0;
     for (int c = 0; c <= D; ++c) a.seg_g[c] = (int64_t)c * G / D;
     for (int c = 0; c < D; ++c) {
-        max_gc = std::max(max_gc, a.seg_g[c + 1] - a.seg_g[c]);
         a.f_gc[c] = make_fastdiv32((uint32_t)std::max<int64_t>(1, a.seg_g[c + 1] - a.seg_g[c]));
         a.side[c] = (uint32_t)p->dims[c];
         a.stride[c] = (uint32_t)p->strides[c];
@@ -382,7 +374,6 @@ int run_fold_dims(T* buf, int64_t elems, const trivance_plan_t* p, hipStream_t s
         if (p->placed)
             for (int t = 0; t < p->S; ++t) a.pdim[c] |= (uint32_t)p->passes[t].dim[c] << (4 * t);
     }
-    a.narrow = (int64_t)p->n * (max_gc + 1) < ((int64_t)1 << 31) ? 1 : 0;
     // programs: all in one launch, or one launch per collective
     const bool together = fold_together(p);
     for (int c0 = 0; c0 < D; c0 += together ? D : 1) {

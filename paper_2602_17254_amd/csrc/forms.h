@@ -121,9 +121,12 @@ inline bool fold_together(const trivance_plan_t* p) {
     return words <= kMaxFoldWords;
 }
 
+// Rows below 1 GiB (32-bit offsets), and n rows of granules counted in 31 bits (the block of a column,
+// and the units of the spread; 550 GB of vectors). The tiles above stay within both by their limits.
 inline bool fold_fits(const trivance_plan_t* p, int64_t elems) {
+    const int64_t granules = (elems + kGranule - 1) / kGranule;
     return !p->folds.empty() && elems < ((int64_t)1 << 28) &&
-           (int64_t)p->n * ((elems + kSpreadTile - 1) / kSpreadTile + 1) < ((int64_t)1 << 31) - 4;
+           (int64_t)p->n * (granules + 1) < ((int64_t)1 << 31) - 4;
 }
 
 // ---- latency-optimal calls: all steps in local memory (sweep.hip) ----

@@ -80,7 +80,6 @@ constexpr int kMaxFoldRanks = 8192;
 constexpr int kMaxFoldRoots = 512;
 constexpr size_t kMaxFoldWords = 896;      // words that fit the kernel arguments
 struct FoldProgram {
-    int cut = 0;
     int sub_depth = 0, top_depth = 0;      // open sums below the current one, at most
     std::vector<uint32_t> roots;           // subtrees in preorder: offset, and what follows
     std::vector<uint32_t> shape;           // subtree -> its shape

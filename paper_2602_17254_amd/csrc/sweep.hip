@@ -312,7 +312,6 @@ int run_sweep_dims(T* buf, int64_t elems, const trivance_plan_t* p, hipStream_t 
     const bool loop = a.grid < tiles;
     if (s.ops == 1) {
         switch (s.cells) {
-            case 1: err = launch_sweep<T, D, 1, 1, false>(buf, a, s, x); break;
             case 2: err = launch_sweep<T, D, 2, 1, false>(buf, a, s, x); break;
             case 4: err = launch_sweep<T, D, 4, 1, false>(buf, a, s, x); break;
         }

@@ -20,7 +20,6 @@ struct TileArgs {
     int64_t elems;
     int64_t seg_g[kMaxFoldDims + 1];
     uint32_t n;
-    int narrow;                          // 1 if n * (granules of a segment + 1) < 2^31
     uint32_t side[kMaxFoldDims], stride[kMaxFoldDims];
     FastDiv32 f_side[kMaxFoldDims];
     FastDiv32 f_gc[kMaxFoldDims];        // granules of segment c
@@ -87,10 +86,7 @@ __global__ __launch_bounds__(1024) void tile_kernel(T* __restrict__ buf, TileArg
         // the block of the cell's columns (columns past the segment's end take its last block)
         const int64_t in = imin64(col0 - seg_b + vec[k] * 4, col0 - seg_b + left - 1);
         const uint32_t gr = (uint32_t)(in / kGranule);
-        uint32_t j;
-        if (a.narrow) j = fdiv32((gr + 1) * a.n - 1, a.f_gc[c]);
-        else j = (uint32_t)(((uint64_t)(gr + 1) * a.n - 1) /
-                            (uint64_t)(a.seg_g[c + 1] - a.seg_g[c]));
+        uint32_t j = fdiv32((gr + 1) * a.n - 1, a.f_gc[c]);
         uint32_t y[D] = {};
         if (a.placed) {
             // j is the block's position: its base-3 digits, the last step's lowest
@@ -199,11 +195,9 @@ int run_tile_dims(T* buf, int64_t elems, const trivance_plan_t* p, hipStream_t s
     a.cells = (uint32_t)p->n << s.shift;
     const int64_t G = (elems + kGranule - 1) / kGranule;
     for (int c = 0; c <= D; ++c) a.seg_g[c] = (int64_t)c * G / D;
-    int64_t max_gc = 0;
     uint32_t tiles = 0;
     for (int c = 0; c < D; ++c) {
         const int64_t gc = a.seg_g[c + 1] - a.seg_g[c];
-        max_gc = std::max(max_gc, gc);
         a.f_gc[c] = make_fastdiv32((uint32_t)std::max<int64_t>(1, gc));
         a.side[c] = (uint32_t)p->dims[c];
         a.stride[c] = (uint32_t)p->strides[c];
@@ -215,7 +209,6 @@ int run_tile_dims(T* buf, int64_t elems, const trivance_plan_t* p, hipStream_t s
         tiles += (uint32_t)(((len + 3) / 4 + ((int64_t)1 << s.shift) - 1) >> s.shift);
         a.tile_end[c] = tiles;
     }
-    a.narrow = (int64_t)p->n * (max_gc + 1) < ((int64_t)1 << 31) ? 1 : 0;
     std::copy(p->tile_masks.begin(), p->tile_masks.end(), a.tab);
     hipError_t err;
     switch (s.cells) {

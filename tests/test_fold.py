@@ -113,6 +113,8 @@ def test_cases_reach_every_form(tmp_path):
             assert any(f.startswith(f"fold w{waves} ") and launches in f for f in seen)
     for waves in (1, 16):
         assert any(f.startswith(f"fold w{waves} ") and "per-collective" in f for f in seen)
+    # more columns than the block index counts (880 GB)
+    assert forms(tmp_path, [("B", (6561,), "natural", 1 << 25)]) == ["steps"]
     # tiles at their narrowest and widest
     assert {"fold w4 v32 one", "fold w4 v64 one", "fold w16 v4 one", "fold w16 v64 spread"} <= seen
 

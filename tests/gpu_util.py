@@ -13,10 +13,29 @@ from oracle import allreduce, nonpow3, partition, schedule
 VARIANT_NAMES = {"L": "latency-optimal", "B": "bandwidth-optimal"}
 
 
+# A whole AllReduce through the whole-call entry points, which run the fused kernels where they fit,
+# and through the step-range ones, which run every pass by the step kernels.
+FORMS = ("whole", "steps")
+
+
+def enqueue(buf, plan, ws=None, stream=None, form: str = "whole") -> None:
+    import paper_2602_17254_amd as T
+
+    if form == "whole" and ws is None:
+        T.trivance_allreduce_emulated(buf, plan, stream)
+    elif form == "whole":
+        T.trivance_allreduce_emulated_ws(buf, plan, ws, stream)
+    elif ws is None:
+        T.trivance_allreduce_emulated_steps(buf, plan, 0, plan.num_passes, stream)
+    else:
+        T.trivance_allreduce_emulated_steps_ws(buf, plan, ws, 0, plan.num_passes, stream)
+
+
 def run_hip(V: np.ndarray, dims, variant: str, placement: str = "natural",
             dispatch_items: int | None = None) -> np.ndarray:
-    """Run the HIP path on a copy of V; with dispatch_items, on a plan whose launches are split
-    into dispatches of at most that many work-items."""
+    """Run the HIP path on copies of V, as a whole call and step by step, which must leave the same
+    bits; with dispatch_items, on a plan whose launches are split into dispatches of at most that
+    many work-items."""
     import torch
 
     import paper_2602_17254_amd as T
@@ -24,17 +43,24 @@ def run_hip(V: np.ndarray, dims, variant: str, placement: str = "natural",
     plan = T.trivance_plan(dims, variant, placement)
     if dispatch_items is not None:
         plan = T.trivance_plan_with_dispatch_limit(plan, dispatch_items)
-    buf = torch.from_numpy(np.ascontiguousarray(V)).cuda()
     ws_bytes = T.trivance_workspace_bytes(plan, V.shape[1])
-    if ws_bytes:
+    got = {}
+    for form in FORMS:
+        buf = torch.from_numpy(np.ascontiguousarray(V)).cuda()
         # the partial sums of the latency-optimal variant on sides that are not powers of three;
         # filled with NaN so that a read of stale contents would show
-        ws = torch.full(((ws_bytes + 3) // 4,), float("nan"), dtype=torch.float32, device="cuda")
-        T.trivance_allreduce_emulated_ws(buf, plan, ws)
+        ws = None
+        if ws_bytes:
+            ws = torch.full(((ws_bytes + 3) // 4,), float("nan"), dtype=torch.float32, device="cuda")
+        enqueue(buf, plan, ws, form=form)
+        torch.cuda.synchronize()
+        got[form] = buf.cpu().numpy()
+    what = f"{dims} {variant}: step by step against the whole call"
+    if V.dtype == np.int32:
+        np.testing.assert_array_equal(got["steps"], got["whole"], what)
     else:
-        T.trivance_allreduce_emulated(buf, plan)
-    torch.cuda.synchronize()
-    return buf.cpu().numpy()
+        assert_same_bits(got["steps"], got["whole"], what)
+    return got["whole"]
 
 
 def assert_matches_oracle(got: np.ndarray, V: np.ndarray, dims, variant: str, col_seg=None,
@@ -87,7 +113,7 @@ def assert_same_bits(got: np.ndarray, want: np.ndarray, what: str = "") -> None:
     w = np.ascontiguousarray(want).view(np.uint32)
     both_nan = np.isnan(got) & np.isnan(want)
     bad = np.argwhere((g != w) & ~both_nan)
-    assert bad.size == 0, (f"{what}: fp32 differs in bits from the schedule-ordered oracle at "
+    assert bad.size == 0, (f"{what}: fp32 differs in bits at "
                            f"{bad[:5].tolist()}")
 
 

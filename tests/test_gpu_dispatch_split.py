@@ -2,9 +2,11 @@
 
 A dispatch carries its grid size as a 32-bit count of work-items; every launch of the library
 goes through a split into dispatches of at most the plan's limit (2^31 work-items, lowered on a
-derived plan by trivance_plan_with_dispatch_limit). Here a limit of 1024 work-items (one to sixteen workgroups per dispatch) forces the split on small
-inputs for every kernel family, against the oracle; and a bandwidth-optimal call whose first
-pass holds 3^18 waves (2.5e10 work-items) runs at the default limit, against exact column sums.
+derived plan by trivance_plan_with_dispatch_limit). Here a limit of 1024 work-items (one to sixteen
+workgroups per dispatch) forces the split on small inputs, as whole calls and step by step for every
+step-kernel family, against the oracle; and a bandwidth-optimal call on more ranks than the whole-call
+forms take, whose first pass holds 3^18 waves (2.5e10 work-items), runs at the default limit, against
+exact column sums.
 """
 
 import sys
@@ -34,7 +36,7 @@ def _gpu_present():
     yield
 
 
-# every launch path: latency steps with 3-, 9- (three waves per cycle on rings, one on tori of
+# every launch path of the steps (run_hip runs them beside the whole call): latency steps with 3-, 9- (three waves per cycle on rings, one on tori of
 # three or more dimensions), 27-, 81-, 243- and 729-rank cycles and the generic cycle kernel
 # (2187); block steps; tree steps on rings and tori, with the short and the long offset table. The 10 x 10 x 10 torus takes 65,536 work-items per dispatch
 # (about 500 dispatches per pass), the others 1024.

@@ -1,8 +1,10 @@
 """GPU parity on paths and values the other tests leave out.
 
-* The generic latency-optimal kernel (cycles of 2187 ranks and more) on the 16-byte path: rings
-  of 2187 and a 2187 x 3 torus with E % 4 == 0, fp32 and int32, in full.
-* IEEE fp32 specials through every kernel family (latency-optimal steps, block steps, tree steps):
+* The generic latency-optimal step kernel (cycles of 2187 ranks and more) on the 16-byte path: rings
+  of 2187 (whose whole call is a column program) and a 2187 x 3 torus with E % 4 == 0, fp32 and
+  int32, in full.
+* IEEE fp32 specials through the whole calls and every step-kernel family (latency-optimal, slot,
+  block and tree steps):
   subnormal inputs (from 2^-149 up to about 1e-38), signed zeros, sums that overflow to +/-inf,
   inf - inf and NaN inputs. The oracle adds in numpy float32 (IEEE round-to-nearest-even, no
   flush to zero); the results must agree bit for bit, a NaN matching any NaN (the GPU and the
@@ -17,7 +19,7 @@ import numpy as np
 import pytest
 
 from gpu_util import assert_matches_oracle, assert_same_bits, run_hip
-from oracle import allreduce, nonpow3, partition
+from oracle import allreduce, latency_nonpow3, nonpow3, partition
 from paper_2602_17254_amd import inputs
 
 pytestmark = pytest.mark.gpu
@@ -94,6 +96,8 @@ def _special_inputs(n: int, E: int, seed: int) -> np.ndarray:
 
 def _oracle(V, dims, variant):
     with np.errstate(over="ignore", invalid="ignore"):
+        if variant == "L" and nonpow3.is_tree(dims):
+            return latency_nonpow3.latency_optimal(V, dims)
         if variant == "L":
             return allreduce.latency_optimal(V, dims)
         if nonpow3.is_tree(dims):
@@ -108,7 +112,8 @@ SPECIAL_CASES = [((9,), "L", 64 * 9 + 36), ((27,), "L", 64 * 27 * 2 + 12), ((9, 
                  ((27,), "B", 64 * 27 * 3 + 8), ((243,), "B", 64 * 243 + 4), ((9, 9), "B", 64 * 81 * 2),
                  ((3, 3, 3), "B", 64 * 27 * 3 + 20), ((8,), "B", 64 * 8 * 4 + 4),
                  ((64,), "B", 64 * 64 * 2 + 8), ((4, 8), "B", 64 * 32 * 2 * 2 + 12),
-                 ((9,), "L", 1001), ((8,), "B", 999)]
+                 ((9,), "L", 1001), ((8,), "B", 999), ((8,), "L", 64 * 8 * 4 + 4),
+                 ((4, 4), "L", 1003), ((40,), "B", 160_001)]
 
 
 @pytest.mark.parametrize("dims,variant,E", SPECIAL_CASES,

@@ -1,7 +1,7 @@
 """GPU parity of the latency-optimal variant on rings and tori whose sides are not all powers of
-three (Sec. 4.2 with Sec. 4.4): the slot-step kernels through the C ABI against the oracle
-(oracle/latency_nonpow3.py), element by element; int32 bit-exact, fp32 identical bits (and within
-the summation bound). The workspace is filled with NaN before every call, so a read of stale
+three (Sec. 4.2 with Sec. 4.4): whole calls and the slot-step kernels through the C ABI against the
+oracle (oracle/latency_nonpow3.py), element by element; int32 bit-exact, fp32 identical bits (and
+within the summation bound). The workspace is filled with NaN before every call, so a read of stale
 partials would show.
 """
 
@@ -10,7 +10,7 @@ import sys
 import numpy as np
 import pytest
 
-from gpu_util import assert_matches_oracle, run_hip
+from gpu_util import FORMS, assert_matches_oracle, enqueue, run_hip
 from oracle import allreduce, congestion, latency_nonpow3
 
 pytestmark = pytest.mark.gpu
@@ -91,24 +91,25 @@ def test_latency_nonpow3_pass_ranges_and_split_dispatches(dims):
 
 
 def test_latency_nonpow3_misaligned_rows_and_workspace():
-    """A [n, E] view that is not 16-byte aligned, and a workspace that is not either: the scalar
-    path gives the same bits."""
+    """A [n, E] view that is not 16-byte aligned, and a workspace that is not either: the whole call
+    and the scalar path of the steps give the oracle's bits."""
     import paper_2602_17254_amd as T
 
     dims, E = (7,), 64 * 7 * 2 + 8
     n = 7
     V = np.random.default_rng(77).standard_normal((n, E)).astype(np.float32)
     plan = T.trivance_plan(dims, "L")
-    flat = torch.zeros(n * E + 1, dtype=torch.float32, device="cuda")
-    view = flat[1:].view(n, E)
-    view.copy_(torch.from_numpy(V))
-    nws = (T.trivance_workspace_bytes(plan, E) + 3) // 4
-    wflat = torch.full((nws + 1,), float("nan"), dtype=torch.float32, device="cuda")
-    ws = wflat[1:]
-    assert view.data_ptr() % 16 != 0 and ws.data_ptr() % 16 != 0
-    T.trivance_allreduce_emulated_ws(view, plan, ws)
-    torch.cuda.synchronize()
-    assert_matches_oracle(view.cpu().numpy(), V, dims, "L", what="misaligned L 7")
+    for form in FORMS:
+        flat = torch.zeros(n * E + 1, dtype=torch.float32, device="cuda")
+        view = flat[1:].view(n, E)
+        view.copy_(torch.from_numpy(V))
+        nws = (T.trivance_workspace_bytes(plan, E) + 3) // 4
+        wflat = torch.full((nws + 1,), float("nan"), dtype=torch.float32, device="cuda")
+        ws = wflat[1:]
+        assert view.data_ptr() % 16 != 0 and ws.data_ptr() % 16 != 0
+        enqueue(view, plan, ws, form=form)
+        torch.cuda.synchronize()
+        assert_matches_oracle(view.cpu().numpy(), V, dims, "L", what=f"misaligned L 7 {form}")
 
 
 @pytest.mark.parametrize("dims", [(8,), (7,), (32,), (64,), (4, 4), (5, 7), (32, 32), (8, 64)],

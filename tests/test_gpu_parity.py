@@ -1,4 +1,5 @@
-"""GPU parity: the HIP path (through the C ABI) against the CPU oracle, element by element.
+"""GPU parity: the HIP path (through the C ABI) against the CPU oracle, element by element, as whole
+calls and step by step.
 
 Run on an MI355X: python -u -m pytest tests -m gpu -x -v --timeout 120 --timeout-method thread
 Bars: int32 and congestion bit-exact; fp32 within 1e-6 relative of the schedule-ordered oracle
@@ -10,7 +11,7 @@ import sys
 import numpy as np
 import pytest
 
-from gpu_util import assert_matches_oracle, run_hip
+from gpu_util import FORMS, assert_matches_oracle, enqueue, run_hip
 from oracle import allreduce, congestion, partition, schedule
 
 pytestmark = pytest.mark.gpu
@@ -97,24 +98,24 @@ def test_parity_latency_4d_torus(dtype):
 @pytest.mark.parametrize("dims,variants", [((9,), "LB"), ((8,), "B"), ((4, 4), "B"), ((81,), "L"),
                                            ((243,), "L"), ((3, 9, 9), "LB")])
 def test_misaligned_rows_use_scalar_path(dims, variants):
-    """A [n, E] view whose start is not 16-byte aligned still gives the oracle's result (block,
-    latency and tree steps; latency tiles of 3-, 9-, 81- and 243-row cycles, with one and with
-    several waves per cycle)."""
+    """A [n, E] view whose start is not 16-byte aligned still gives the oracle's result: whole calls,
+    and the scalar path of the block, latency and tree steps (latency tiles of 3-, 9-, 81- and
+    243-row cycles, with one and with several waves per cycle)."""
     import paper_2602_17254_amd as T
 
     n = int(np.prod(dims))
     E = 64 * n * len(dims) * 2 + 8
     rng = np.random.default_rng(3)
     V = rng.standard_normal((n, E), dtype=np.float32)
-    for variant in variants:
-        _say(f"[misaligned] dims={dims} variant={variant}")
+    for variant, form in [(v, f) for v in variants for f in FORMS]:
+        _say(f"[misaligned] dims={dims} variant={variant} form={form}")
         flat = torch.zeros(n * E + 1, dtype=torch.float32, device="cuda")
         view = flat[1:].view(n, E)
         view.copy_(torch.from_numpy(V))
         assert view.data_ptr() % 16 != 0
-        T.trivance_allreduce_emulated(view, T.trivance_plan(dims, variant))
+        enqueue(view, T.trivance_plan(dims, variant), form=form)
         torch.cuda.synchronize()
-        assert_matches_oracle(view.cpu().numpy(), V, dims, variant, what="misaligned")
+        assert_matches_oracle(view.cpu().numpy(), V, dims, variant, what=f"misaligned {form}")
 
 
 @pytest.mark.parametrize("dims", [(27,), (9, 9), (3, 3, 3), (3, 9)])
@@ -263,7 +264,8 @@ NONPOW3 = [(2, 100), (4, 64 * 4 * 3 + 4), (5, 999), (7, 64 * 7 * 5 + 12), (8, 64
 @pytest.mark.parametrize("dtype", ["f32", "i32"])
 @pytest.mark.parametrize("n,E", NONPOW3, ids=[f"n{n}-E{E}" for n, E in NONPOW3])
 def test_parity_nonpower3_ring(n, E, dtype):
-    """Sec. 4.4 rings (bandwidth-optimal): the tree-driven kernels against the oracle."""
+    """Sec. 4.4 rings (bandwidth-optimal): the whole call and the tree-driven steps against the
+    oracle."""
     rng = np.random.default_rng(n * 7 + E)
     _say(f"[nonpow3] n={n} E={E} dtype={dtype}")
     if dtype == "f32":
@@ -388,16 +390,18 @@ def test_parity_largest_rings_sampled(n):
             V = rng.standard_normal((n, E), dtype=np.float32)
         else:
             V = rng.integers(-(2 ** 31), 2 ** 31 - 1, size=(n, E), dtype=np.int32)
-        buf = torch.from_numpy(V).cuda()
-        T.trivance_allreduce_emulated(buf, plan)
-        torch.cuda.synchronize()
-        got = buf.index_select(1, torch.from_numpy(cols).cuda()).cpu().numpy()
-        assert_matches_oracle(got, np.ascontiguousarray(V[:, cols]), (n,), "B", col_seg=seg,
-                              col_blk=blk, what=f"ring {n} {dtype}")
-        del buf
+        for form in FORMS:
+            buf = torch.from_numpy(V).cuda()
+            enqueue(buf, plan, form=form)
+            torch.cuda.synchronize()
+            got = buf.index_select(1, torch.from_numpy(cols).cuda()).cpu().numpy()
+            assert_matches_oracle(got, np.ascontiguousarray(V[:, cols]), (n,), "B", col_seg=seg,
+                                  col_blk=blk, what=f"ring {n} {dtype} {form}")
+            del buf
 
 
-def test_two_streams_concurrently():
+@pytest.mark.parametrize("form", FORMS)
+def test_two_streams_concurrently(form):
     """Independent AllReduces enqueued on two streams (default priority) both match the oracle."""
     import paper_2602_17254_amd as T
 
@@ -412,16 +416,17 @@ def test_two_streams_concurrently():
     torch.cuda.synchronize()
     for (dims, variant, V, buf), s in zip(data, streams):
         _say(f"[streams] {dims} {variant}")
-        T.trivance_allreduce_emulated(buf, T.trivance_plan(dims, variant), stream=s)
+        enqueue(buf, T.trivance_plan(dims, variant), stream=s, form=form)
     for s in streams:
         s.synchronize()
     for dims, variant, V, buf in data:
         assert_matches_oracle(buf.cpu().numpy(), V, dims, variant, what=f"stream {dims}")
 
 
+@pytest.mark.parametrize("form", FORMS)
 @pytest.mark.parametrize("dims,variant", [((27,), "B"), ((9,), "L"), ((3, 8), "B"), ((9, 9), "B")])
-def test_graph_capture_replays(dims, variant):
-    """The enqueued passes can be captured in a HIP graph: every replay (with eager refills and
+def test_graph_capture_replays(dims, variant, form):
+    """The enqueued launches can be captured in a HIP graph: every replay (with eager refills and
     synchronisation between replays) reproduces the eager result bit for bit."""
     import paper_2602_17254_amd as T
 
@@ -431,7 +436,7 @@ def test_graph_capture_replays(dims, variant):
     V = np.random.default_rng(n + E).standard_normal((n, E), dtype=np.float32)
     src = torch.from_numpy(V).cuda()
     buf = src.clone()
-    T.trivance_allreduce_emulated(buf, plan)
+    enqueue(buf, plan, form=form)
     torch.cuda.synchronize()
     eager = buf.clone()
     s = torch.cuda.Stream()
@@ -439,7 +444,7 @@ def test_graph_capture_replays(dims, variant):
     buf.copy_(src)
     torch.cuda.synchronize()
     with torch.cuda.graph(g, stream=s):
-        T.trivance_allreduce_emulated(buf, plan)
+        enqueue(buf, plan, form=form)
     for k in range(3):
         _say(f"[graph] {dims} {variant} replay {k}")
         buf.copy_(src)
@@ -490,16 +495,17 @@ def test_placed_misaligned_rows_use_scalar_path(dims):
     n = int(np.prod(dims))
     E = 64 * n * len(dims) * 2 + 8
     V = np.random.default_rng(5).standard_normal((n, E), dtype=np.float32)
-    _say(f"[placed misaligned] dims={dims}")
-    flat = torch.zeros(n * E + 1, dtype=torch.float32, device="cuda")
-    view = flat[1:].view(n, E)
-    view.copy_(torch.from_numpy(V))
-    assert view.data_ptr() % 16 != 0
-    T.trivance_allreduce_emulated(view, T.trivance_plan(dims, "B", placement="schedule"))
-    torch.cuda.synchronize()
     seg, blk = placement_labels(E, dims)
-    assert_matches_oracle(view.cpu().numpy(), V, dims, "B", col_seg=seg, col_blk=blk,
-                          what="placed misaligned")
+    for form in FORMS:
+        _say(f"[placed misaligned] dims={dims} form={form}")
+        flat = torch.zeros(n * E + 1, dtype=torch.float32, device="cuda")
+        view = flat[1:].view(n, E)
+        view.copy_(torch.from_numpy(V))
+        assert view.data_ptr() % 16 != 0
+        enqueue(view, T.trivance_plan(dims, "B", placement="schedule"), form=form)
+        torch.cuda.synchronize()
+        assert_matches_oracle(view.cpu().numpy(), V, dims, "B", col_seg=seg, col_blk=blk,
+                              what=f"placed misaligned {form}")
 
 
 @pytest.mark.parametrize("dims", [(27,), (9, 9), (3, 3, 3)])

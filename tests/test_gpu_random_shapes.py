@@ -1,6 +1,6 @@
 """Parity on a seeded random sample of shapes: rings and tori of one to three dimensions with sides
-of 1 to 30 (powers of three or not, equal or not), both variants, fp32 and int32, against the
-oracle element by element (fp32 identical bits, int32 exact).
+of 1 to 30 (powers of three or not, equal or not), both variants, fp32 and int32, as whole calls and
+step by step, against the oracle element by element (fp32 identical bits, int32 exact).
 
 The sample (128 shapes) is drawn once from a fixed seed, so every case has a stable name; it
 complements the hand-picked shapes of the other parity tests with combinations nobody chose:

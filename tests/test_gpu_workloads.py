@@ -1,4 +1,5 @@
-"""GPU parity at the five named workload sizes, through the same entry point the benchmark times.
+"""GPU parity at the named workload sizes, as whole calls and step by step (the entry points that the
+benchmark times).
 
 Small workloads are compared in full; large ones on a deterministic column sample (for the
 bandwidth-optimal variant: first, last and two random elements of every block of every segment;
@@ -11,7 +12,7 @@ import sys
 import numpy as np
 import pytest
 
-from gpu_util import assert_matches_oracle, sample_columns
+from gpu_util import FORMS, assert_matches_oracle, enqueue, sample_columns
 from oracle import congestion
 from paper_2602_17254_amd import inputs
 
@@ -26,13 +27,21 @@ def _say(msg):
 
 
 def _run_full(w, V):
+    """The whole call's result, which the step-by-step run has to equal in every element."""
     import paper_2602_17254_amd as T
 
     plan = T.trivance_plan(w.dims, w.variant, w.placement)
-    buf = torch.from_numpy(V).cuda()
-    T.trivance_allreduce_emulated(buf, plan)
-    torch.cuda.synchronize()
-    return buf
+    need = T.trivance_workspace_bytes(plan, w.elems)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda") if need else None
+    bufs = []
+    for form in FORMS:
+        bufs.append(torch.from_numpy(V).cuda())
+        enqueue(bufs[-1], plan, ws, form=form)
+        torch.cuda.synchronize()
+    whole, steps = bufs
+    for r in range(w.n):  # row by row: the comparison of all at once takes a third buffer
+        assert torch.equal(whole[r].view(torch.int32), steps[r].view(torch.int32)), f"{w.name} rank {r}"
+    return whole
 
 
 def _check_sampled(w, V, buf, seed):
@@ -103,21 +112,9 @@ def test_torus27x27_bandwidth_4MiB():
 
 
 def test_torus9x9x9_bandwidth_128MiB():
-    import paper_2602_17254_amd as T
-
     w = inputs.WORKLOADS["torus9x9x9_B_128MiB"]
     _say(f"[workload] {w.name} f32, device-generated inputs (column sample)")
-    buf = torch.empty((w.n, w.elems), dtype=torch.float32, device="cuda")
-    T.trivance_fill_hash_uniform(buf, w.seed)
-    plan = T.trivance_plan(w.dims, w.variant)
-    T.trivance_allreduce_emulated(buf, plan)
-    torch.cuda.synchronize()
-    cols, seg, blk = sample_columns(w.elems, 3, w.n, w.variant, w.seed)
-    got = buf.index_select(1, torch.from_numpy(cols).cuda()).cpu().numpy()
-    Vs = inputs.hash_uniform(w.seed, w.elems, np.arange(w.n), cols)
-    assert_matches_oracle(got, Vs, w.dims, w.variant, col_seg=seg, col_blk=blk, what=w.name)
-    del buf
-    torch.cuda.empty_cache()
+    _device_hash_workload(w)
 
 
 def test_ring8_bandwidth_32MiB_nonpower3():
@@ -144,22 +141,32 @@ def test_ring64_bandwidth_8MiB_nonpower3():
 
 
 def _device_hash_workload(w, max_blocks=None):
-    """Device-generated U(-1, 1) inputs, one run, then a column sample against the oracle (the
-    gather form on the sampled columns with their block labels) and identical bits on all ranks."""
+    """Device-generated U(-1, 1) inputs, run as a whole call and step by step, each with a column
+    sample against the oracle (the gather form on the sampled columns with their block labels); after a
+    bandwidth-optimal call all ranks hold identical bits."""
     import paper_2602_17254_amd as T
 
     D = len(w.dims)
     buf = torch.empty((w.n, w.elems), dtype=torch.float32, device="cuda")
-    T.trivance_fill_hash_uniform(buf, w.seed)
     plan = T.trivance_plan(w.dims, w.variant, w.placement)
-    T.trivance_allreduce_emulated(buf, plan)
-    torch.cuda.synchronize()
     cols, seg, blk = sample_columns(w.elems, D, w.n, w.variant, w.seed, max_blocks=max_blocks,
                                     dims=w.dims, placement=w.placement)
-    got = buf.index_select(1, torch.from_numpy(cols).cuda()).cpu().numpy()
     Vs = inputs.hash_uniform(w.seed, w.elems, np.arange(w.n), cols)
-    assert_matches_oracle(got, Vs, w.dims, w.variant, col_seg=seg, col_blk=blk, what=w.name)
-    assert bool((buf[1:] == buf[0:1]).all().item())
+    got = {}
+    for form in FORMS:
+        T.trivance_fill_hash_uniform(buf, w.seed)
+        need = T.trivance_workspace_bytes(plan, w.elems)
+        ws = torch.empty(need, dtype=torch.uint8, device="cuda") if need else None
+        enqueue(buf, plan, ws, form=form)
+        torch.cuda.synchronize()
+        del ws
+        torch.cuda.empty_cache()
+        got[form] = buf.index_select(1, torch.from_numpy(cols).cuda()).cpu().numpy()
+        if w.variant == "B":
+            assert all(torch.equal(row, buf[0]) for row in buf)
+    assert np.array_equal(got["steps"].view(np.uint32), got["whole"].view(np.uint32))
+    assert_matches_oracle(got["whole"], Vs, w.dims, w.variant, col_seg=seg,
+                          col_blk=blk if w.variant == "B" else None, what=w.name)
     del buf
     torch.cuda.empty_cache()
 
@@ -186,50 +193,23 @@ def test_torus16x16x16_bandwidth_8MiB_nonpower3():
 
 
 # The latency-optimal variant on sides that are not powers of three (partials in a workspace).
-def _run_full_ws(w, buf):
-    import paper_2602_17254_amd as T
-
-    plan = T.trivance_plan(w.dims, w.variant, w.placement)
-    ws = torch.empty(T.trivance_workspace_bytes(plan, w.elems), dtype=torch.uint8, device="cuda")
-    T.trivance_allreduce_emulated_ws(buf, plan, ws)
-    torch.cuda.synchronize()
-    del ws
-    torch.cuda.empty_cache()
-    return buf
-
-
 def test_ring8_latency_8MiB_nonpower3():
     w = inputs.WORKLOADS["ring8_L_8MiB"]
     _say(f"[workload] {w.name} f32 (full comparison)")
     V = inputs.normal_f32(w.seed, w.n, w.elems)
-    buf = _run_full_ws(w, torch.from_numpy(V).cuda())
+    buf = _run_full(w, V)
     assert_matches_oracle(buf.cpu().numpy(), V, w.dims, w.variant, what=w.name)
     _say(f"[workload] {w.name} i32 (full comparison)")
     Vi = inputs.uniform_i32(w.int_seed, w.n, w.elems, *w.int_range)
-    buf = _run_full_ws(w, torch.from_numpy(Vi).cuda())
+    buf = _run_full(w, Vi)
     assert_matches_oracle(buf.cpu().numpy(), Vi, w.dims, w.variant, what=w.name)
     _congestion(w)
-
-
-def _device_hash_latency(w):
-    import paper_2602_17254_amd as T
-
-    D = len(w.dims)
-    buf = torch.empty((w.n, w.elems), dtype=torch.float32, device="cuda")
-    T.trivance_fill_hash_uniform(buf, w.seed)
-    _run_full_ws(w, buf)
-    cols, seg, _ = sample_columns(w.elems, D, w.n, "L", w.seed)
-    got = buf.index_select(1, torch.from_numpy(cols).cuda()).cpu().numpy()
-    del buf
-    torch.cuda.empty_cache()
-    Vs = inputs.hash_uniform(w.seed, w.elems, np.arange(w.n), cols)
-    assert_matches_oracle(got, Vs, w.dims, w.variant, col_seg=seg, what=w.name)
 
 
 def test_ring64_latency_8MiB_nonpower3():
     w = inputs.WORKLOADS["ring64_L_8MiB"]
     _say(f"[workload] {w.name} f32, device-generated inputs (column sample)")
-    _device_hash_latency(w)
+    _device_hash_workload(w)
     _congestion(w)
 
 
@@ -238,7 +218,7 @@ def test_torus32x32_latency_8MiB_nonpower3():
     workspace."""
     w = inputs.WORKLOADS["torus32x32_L_8MiB"]
     _say(f"[workload] {w.name} f32, device-generated inputs (column sample)")
-    _device_hash_latency(w)
+    _device_hash_workload(w)
     _congestion(w)
 
 

@@ -1,15 +1,17 @@
 """The step kernels write with one of two cache policies, chosen per pass from the pass's
 algorithmic bytes (`kKeepPassBytes` in csrc/device.h): SC1 alone up to the threshold, NT|SC1 above
 it. The policy changes no value, so only the parity tests can show that each compiled form
-computes the same results. This host-side check keeps them covering both: for every kernel family
-the full-size workloads that tests/test_gpu_workloads.py compares with the oracle include a pass on
-each side of the threshold (no GPU needed: plan and byte counts are host calls)."""
+computes the same results. This host-side check keeps them covering both: the full-size workloads,
+which tests/test_gpu_workloads.py runs step by step (beside the whole call, whose kernels have no such
+policy) and compares with the oracle, include for every step-kernel family a pass on each side of the
+threshold (no GPU needed: plan and byte counts are host calls)."""
 
 import os
 import re
 
 import pytest
 
+import gpu_util
 from paper_2602_17254_amd import inputs
 
 T = pytest.importorskip("paper_2602_17254_amd")
@@ -35,6 +37,16 @@ def _family(w):
     if w.variant == "L":
         return "latency tiles" if pow3 else "slot steps"
     return "block steps" if pow3 else "tree steps"
+
+
+def test_full_size_workloads_run_step_by_step():
+    src = open(os.path.join(HERE, "test_gpu_workloads.py")).read()
+    assert "steps" in gpu_util.FORMS
+    for name in inputs.WORKLOADS:
+        assert f'WORKLOADS["{name}"]' in src, name
+    # the two ways a workload runs there, each over both forms
+    assert len(re.findall(r"for form in FORMS:", src)) == 2
+    assert not re.search(r"trivance_allreduce_emulated", src)
 
 
 def test_every_family_meets_both_policies():

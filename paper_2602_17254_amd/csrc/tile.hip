@@ -63,15 +63,8 @@ __global__ __launch_bounds__(1024) void tile_kernel(T* __restrict__ buf, TileArg
     for (int k = 0; k < CELLS; ++k) {
         const uint32_t i = threadIdx.x + k * blockDim.x;
         mine[k] = i < a.cells;
-        uint32_t r = (mine[k] ? i : 0u) >> a.shift;
-        rank[k] = r;
+        rank[k] = (mine[k] ? i : 0u) >> a.shift;
         vec[k] = i & (wv - 1);
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            const uint32_t q = d + 1 < D ? fdiv32(r, a.f_side[d]) : 0u;
-            z[k][d] = r - q * a.side[d];
-            r = q;
-        }
         const T* const q = buf + (int64_t)rank[k] * E + col0 + vec[k] * 4;
         const int64_t l = mine[k] ? left - (int64_t)vec[k] * 4 : 0;
         if (l >= 4) {
@@ -106,6 +99,15 @@ __global__ __launch_bounds__(1024) void tile_kernel(T* __restrict__ buf, TileArg
                 y[d] = j - q * a.side[d];
                 j = q;
             }
+        }
+        // the cell's coordinates, here and not before the row loads (0.1 us of 7.6 on 9x9x9 ranks of
+        // 1000 values)
+        uint32_t r = rank[k];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const uint32_t q = d + 1 < D ? fdiv32(r, a.f_side[d]) : 0u;
+            z[k][d] = r - q * a.side[d];
+            r = q;
         }
         uint32_t own = 0, bits = 0, until = 31;
 #pragma unroll

@@ -8,8 +8,9 @@
  * *virtual* ranks whose vectors all live in one GPU's memory: a "send" is a read of another
  * rank's row. The step-range calls (trivance_allreduce_emulated_steps[_ws]) materialise every step
  * in HBM before the next one starts (the per-step barrier of Sec. 4.3 is a kernel boundary). The
- * whole-call forms perform the same adds in the same association and leave the same bits, and
- * may carry partial sums through several steps on chip.
+ * whole-call forms perform the same adds in the same association and leave the same bits (where a
+ * result is a NaN, both give one, though not always with the same payload), and may carry partial
+ * sums through several steps on chip.
  *
  * Conventions for every function:
  *   - return value 0 (TRIVANCE_OK) on success, a negative trivance_status on failure;
@@ -225,7 +226,8 @@ int trivance_allreduce_emulated(void* buffers, int n, int64_t elems, int dtype,
 
 /* Same, running only passes [pass_begin, pass_end) (0 <= begin <= end <= num_passes); used to
  * inspect or resume the state between steps, and to measure the step-by-step schedule: each pass
- * is one materialised step. Running all ranges back to back equals one full call, bit for bit. */
+ * is one materialised step. Running all ranges back to back equals one full call, bit for bit (NaN
+ * payloads aside). */
 int trivance_allreduce_emulated_steps(void* buffers, int n, int64_t elems, int dtype,
                                       const trivance_plan_t* plan, void* stream, int pass_begin,
                                       int pass_end);

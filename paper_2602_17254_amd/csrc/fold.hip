@@ -21,10 +21,11 @@ namespace {
 // 18 step launches took 22.4 ms, fold and spread take 4.98 (less than
 // the copy's: see the rates of pure reads and pure writes below).
 //  * Two launches. Waves that read their column of all rows and then write it to all rows drift
-//    apart, and with reads and writes of many rows mixed the memory gave 5.0-5.5 TB/s whatever
-//    the store policy, occupancy or batch. Reads alone reach 6.9-7.1, and one-store waves that
-//    walk the rows in address order 7.0-7.4. So the fold only writes row 0, and spread_kernel
-//    copies it. The one-launch form stays for calls below kSpreadBytes.
+//    apart, and with reads and writes of many rows mixed the memory gave 4.9-5.3 TB/s on 240 rows
+//    of 32 MiB and 4.6-5.9 on 16 of 256 MiB, over nine store policies, occupancies, batches,
+//    barriers and pipelined waves. Reads alone reach 6.7-7.2, and one-store waves that walk the
+//    rows in address order 7.0-7.4. So the fold only writes row 0, and spread_kernel copies it. The
+//    one-launch form stays for the calls that fold_spreads (forms.h) names.
 //  * The scalar unit bounds the reads next: a wave's kibibyte may take 91 cycles of its compute
 //    unit, and decoding one row per program word took about as many. One word for the up to
 //    three rows of V(o, 1) cut the read part from 3.58 to 2.69 ms.

@@ -24,7 +24,9 @@ struct TileShape {
 // ranks of 256 values 18 / 6, of 4096 (12 MB) 19 / 10, of 16,384 (48 MB) 23 / 40; 16x16x16 of 256
 // values 107 / 22, of 4096 (67 MB) 129 / 84, of 16,384 174 / 536; rings of 64 and 243 equal at 17 MB.
 // Below, a row is in flight from every thread at once and a step costs 0.4 us; above, the fold
-// reads longer pieces of a row.
+// reads longer pieces of a row. On few ranks with long rows the line lies too high: 4 ranks of 1,048,576
+// values (17 MB) take 6.6 with the fold's waves and 9.2 with the tiles that they get (the steps 15.7),
+// 8 ranks 10.7 and 15.5 at 34 MB, above the line.
 constexpr int64_t kTileBytes = (int64_t)24 << 20;
 constexpr int64_t kTileElems = 4096;
 
@@ -69,7 +71,9 @@ inline size_t fold_lds(const FoldShape& s, size_t roots, int sub_depth, int top_
 // Fold and spread from 192 MiB of vectors on. Measured in us, one launch against two, at 134 MB
 // (ring of 8) 45.7 / 46.3, at 191 MB (27x27) 68.4 / 65.9, at 255 MB (ring of 243) 88 / 81, at 268 MB
 // (rings of 4 and 64) 91 / 81 and 92 / 82: below the size of the 256 MB last-level cache the writes
-// of the one launch end there, and the second launch costs 3 us.
+// of the one launch end there, and the second launch costs 3 us. These are calls on vectors that are not
+// in the cache; on one set of vectors that stays there one launch is the faster up to its size (4 ranks at
+// 255 MB 59 / 77).
 constexpr int64_t kSpreadBytes = (int64_t)192 << 20;
 // Not on two ranks, nor on three whose rows exceed that cache: the second launch reads row 0 once more,
 // a fourth or a sixth on top of the call's traffic, and two launches were slower than the steps. In

@@ -54,8 +54,8 @@ static_assert(sizeof(SweepArgs) <= 4096, "sweep kernel arguments above 4 KiB");
 // OPS operations, whose results stay in registers until every thread has read its terms. LOOP: the
 // workgroup takes several tiles and reads the next one's rows while it works on one.
 //
-// What bounds it (MI355X). Rings of powers of three: the memory, 5.2-5.7 TB/s, which is what
-// waves that read many rows and then write them reach in any arrangement (fold.hip). Ring of 81
+// What bounds it (MI355X). Rings of powers of three: the memory, 5.2-5.7 TB/s, where probes that
+// read many rows and then write them reached 4.6-5.9 (fold.hip). Ring of 81
 // at 8 MiB 263 us, of which one read and one write at a copy's rate are 201; the four step launches
 // took 858. With partial sums: the vector instructions that find the terms and the barriers between
 // levels (ring of 64 at 8 MiB 265 us, steps 2298; 32x32 at 256 KiB 630-665, steps 4346, one

@@ -79,7 +79,8 @@ constexpr int64_t kSpreadBytes = (int64_t)192 << 20;
 // a fourth or a sixth on top of the call's traffic, and two launches were slower than the steps. In
 // us over three sets of vectors in turn, two launches / steps / one: 2 ranks at 403 MB 143 / 141 / 130,
 // at 1600 MB 611 / 598 / 509; 3 ranks at 403 MB 136 / 140 / 145, at 2400 MB 871 / 869 / 815 (as a
-// torus of 1x3 887 / 869 / 799); 4 ranks at 2400 MB 848 / 1357 / 838.
+// torus of 1x3 887 / 869 / 799); 4 ranks at 2400 MB 848 / 1357 / 838. One launch is the slower of the two,
+// though not slower than the steps, on 3 rows 16 bytes short of 1 GiB (1202 / 1350 / 1320).
 constexpr int64_t kLastLevelBytes = (int64_t)256 << 20;
 
 inline bool fold_spreads(int n, int64_t elems) {
